@@ -203,8 +203,10 @@ xg_status xg_preprocess(const xg_frame *f /* [host] */, const xg_gaussians *g /*
  * the status word.  Last, the order in which the blend launches take the
  * tiles: each XCD's contiguous block of tiles (workgroup b runs on XCD
  * b % 8) from the longest list to the shortest, so no long tile starts
- * near the end of a launch; the render calls read it (any order gives the
- * same results). */
+ * near the end of a launch; where those blocks hold very different numbers
+ * of list entries, the tiles are dealt to the XCDs in smaller chunks
+ * instead (an internal copy of the order; any order gives the same
+ * results). */
 xg_status xg_bin_sort(const xg_frame *f /* [host] */, void *stream);
 
 /* Stage 3 (Eq. 10): front-to-back blending of every pixel over its tile's
@@ -337,7 +339,8 @@ typedef struct {
     const float *grad2d;
     int32_t pair_index_bits;
     int64_t total_tiles, total_pixels;
-    const int32_t *tile_order;   /* int32[total_tiles], written by xg_bin_sort */
+    const int32_t *tile_order;   /* int32[total_tiles], written by xg_bin_sort: each XCD's
+                                    contiguous block of tiles, longest list first */
 } xg_ws_view;
 xg_status xg_ws_inspect(const xg_frame *f /* [host] */, xg_ws_view *out /* [host] */);
 

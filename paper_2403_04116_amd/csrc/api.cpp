@@ -73,7 +73,7 @@ xg_status check_frame(const xg_frame *f, bool need_ws, int64_t *tot_px, int64_t 
 struct Plan {
     xg_ws_layout lay;
     size_t icounts, scan_tmp, ikeys[2], ivals[2], ptile[2], pval[2], ghist, vhist, bin_cnt, bin_ptot,
-        bin_pstart, lookback[2], tile_order, xcd_order, ssim, entry_mask;
+        bin_pstart, lookback[2], tile_order, xcd_order, blend_order, ssim, entry_mask;
     int64_t total_px, total_tiles, n_items;
     int32_t item_blocks, pair_blocks, tile_bits, pair_passes, pair_gbits, bin_tiles, bin_ppv;
 };
@@ -137,6 +137,7 @@ xg_status make_plan(const xg_frame *f, bool need_ws, Plan &P) {
     L.grad2d = o;             o = align_up(o + 32 * (size_t)ni);
     P.tile_order = o;         o = align_up(o + 4 * (size_t)P.total_tiles);
     P.xcd_order = o;          o = align_up(o + 4 * (size_t)P.total_tiles);
+    P.blend_order = o;        o = align_up(o + 4 * (size_t)P.total_tiles);
     P.ssim = o;               o = align_up(o + 12 * (size_t)P.total_px + 4 * (size_t)loss_tiles(f->cams, f->n_views));
     L.pair_tiles = P.ptile[P.pair_passes & 1];
     L.pair_values = P.pair_gbits ? P.ptile[P.pair_passes & 1] : P.pval[P.pair_passes & 1];
@@ -176,6 +177,7 @@ Ws resolve(const xg_frame *f, const Plan &P) {
     w.grad2d = (float *)(b + P.lay.grad2d);
     w.tile_order = (int32_t *)(b + P.tile_order);
     w.xcd_order = (int32_t *)(b + P.xcd_order);
+    w.blend_order = (int32_t *)(b + P.blend_order);
     w.ssim = (float *)(b + P.ssim);
     w.cap = f->pair_capacity;
     w.n_items = P.n_items;

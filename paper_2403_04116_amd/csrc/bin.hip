@@ -271,7 +271,8 @@ __global__ __launch_bounds__(NW * kWave, NW == 16 ? 8 : 2) void k_bin_scatter(Ws
     // ranges are final; every status, since the blends read it even when
     // the lists are empty), in slots the partitions leave idle
     if ((int)blockIdx.x < kXcds) {
-        xcd_order_block(ws, blockIdx.x, base, s_lst);
+        static_assert(NW * (LT / 2) >= kOrderGroups && LT >= kOrderBuckets && LT / 2 > NW, "scratch of the order");
+        xcd_order_block(ws, blockIdx.x, base, s_lst, &h16[0][0]);
         return;
     }
     const int part = (int)blockIdx.x - kXcds;

@@ -574,7 +574,8 @@ __global__ __launch_bounds__(1024) void k_tile_order(Ws ws) {
 __global__ __launch_bounds__(1024) void k_xcd_order(Ws ws) {
     __shared__ uint32_t hist[kOrderBuckets];
     __shared__ uint32_t scan_lds[1024 / kWave + 1];
-    xcd_order_block(ws, blockIdx.x, hist, scan_lds);
+    __shared__ uint32_t group[kOrderGroups];
+    xcd_order_block(ws, blockIdx.x, hist, scan_lds, group);
 }
 
 // 64-bit sort keys of the sorted pairs, for inspection: keys[p] =
