@@ -521,53 +521,66 @@ constexpr int kDppQuadXor2 = 0x4E;   // quad_perm [2,3,0,1]
 constexpr int kDppRowRor8 = 0x128;   // row_ror:8
 constexpr int kDppHalfMirror = 0x141; // row_half_mirror
 
-// Wavefront sums of the 7 gradient terms of 2 list entries (acc[e][q]),
-// halving the live values at every step (reduce-scatter).  The steps over
-// lane bits 5 and 4 swap wavefront halves and rows (gfx950 permlane swaps:
-// one swap and one add per pair of values), the lower bits read a partner
-// lane through DPP (two selects and one add per pair).  All VALU, no LDS
-// traffic: 33 instructions (one entry alone takes 19).  Afterwards lane
-// 32 e + 4 q holds value q of entry e (q < 7); a value without a partner at
-// some step is summed in both halves and its upper copy is dropped.
-template <int G>
-struct RedLanes {
-    static_assert(G == 2, "groups of 2 entries");
-    __device__ static int entry(int lane) { return lane >> 5; }
-    __device__ static int word(int lane) { return (lane >> 2) & 7; }
-    __device__ static bool adds(int lane) { return (lane & 3) == 0 && word(lane) < 7; }
-};
+// Sums over a wavefront's 8 x 8 pixels of the 7 gradient terms of 4 list
+// entries.  The terms are gp dx^a dy^b (a + b <= 2) and w, and dy depends
+// on the pixel row only, so the rows are summed first: 4 values per entry
+// (gp, gp dy, gp dy^2, w) over lane bits 5-3, then the row sums times 1, dx,
+// dx^2 over lane bits 2-0.  Both are reduce-scatters, which halve the live
+// values at every step; bits 5 and 4 swap wavefront halves and rows (gfx950
+// permlane swaps: one swap and one add per pair of values), the others read
+// a partner lane through DPP (two selects and one add per pair).  All VALU,
+// no LDS traffic.  The kernel issues VALU most of its cycles, so what counts
+// is instructions: 13 an entry here with the moment products, where forming
+// all 7 terms per pixel and summing two entries together took 21.  200k
+// Gaussians x 8 views of 512 x 512: backward 257 -> 207 us; one such view
+// 81 -> 56 us (with the tiles dealt to the XCDs by work).
+//
+// row_sums: acc[e][q] of entry e -> c[0], c[1] at lane 16 e + 8 h + x:
+// (sum gp, sum gp dy^2) for h = 0, (sum gp dy, sum w) for h = 1, of column x.
+// 30 instructions; an entry's sums depend on its own values alone.
+__device__ __forceinline__ void row_sums(const float (&acc)[4][4], int lane, float (&c)[2]) {
+    float b[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        float a[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[e][q]), __float_as_uint(acc[e + 2][q]),
+                                                            false, false);
+            a[e] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+        }
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a[0]), __float_as_uint(a[1]), false, false);
+        b[q] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+    const bool h = lane & 8;
+    c[0] = (h ? b[1] : b[0]) + XG_DPP(h ? b[0] : b[1], kDppRowRor8);
+    c[1] = (h ? b[3] : b[2]) + XG_DPP(h ? b[2] : b[3], kDppRowRor8);
+}
 
-__device__ __forceinline__ float wave_reduce_group(const float (&acc)[2][7]) {
-    const int lane = lane_id();
-    float b[7];
-#pragma unroll
-    for (int i = 0; i < 7; ++i) {
-        // lanes 0-31 keep entry 0, lanes 32-63 entry 1: b[q]
-        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[0][i]), __float_as_uint(acc[1][i]),
-                                                        false, false);
-        b[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
-    float c[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        // even rows keep q = i, odd rows q = i + 4 (q = 3 twice)
-        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(b[i]), __float_as_uint(b[i < 3 ? i + 4 : 3]),
-                                                        false, false);
-        c[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
-    const bool h3 = lane & 8, h2 = lane & 4;
-    float d[2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-        d[j] = (h3 ? c[j + 2] : c[j]) + XG_DPP(h3 ? c[j] : c[j + 2], kDppRowRor8);
-    float x = (h2 ? d[1] : d[0]) + XG_DPP(h2 ? d[0] : d[1], kDppHalfMirror);
-    x += XG_DPP(x, kDppQuadXor2);
+// column_sums: value v of (c0, c0 dx, c0 dx^2, c1) summed over the columns
+// at the lanes of bits 2-1 = v.
+__device__ __forceinline__ float column_sums(const float (&c)[2], float dx, int lane) {
+    const float m1 = c[0] * dx, m2 = m1 * dx;
+    const bool h2 = lane & 4, h1 = lane & 2;
+    const float d0 = (h2 ? m2 : c[0]) + XG_DPP(h2 ? c[0] : m2, kDppHalfMirror);
+    const float d1 = (h2 ? c[1] : m1) + XG_DPP(h2 ? m1 : c[1], kDppHalfMirror);
+    float x = (h1 ? d1 : d0) + XG_DPP(h1 ? d0 : d1, kDppQuadXor2);
     x += XG_DPP(x, kDppQuadXor1);
     return x;
 }
 
-// List entries whose gradient terms are summed over the wavefront together.
-constexpr int kBwdGroup = 2;
+// List entries whose gradient terms are summed over the wavefront together,
+// entry e's sums ending in its row of 16 lanes.
+constexpr int kBwdGroup = 4;
+
+// Gradient word (of the 8 per (view, Gaussian)) that a lane's sum adds to;
+// -1: none (the upper lane of a pair, and the column sum of gp dx^2 dy).
+__device__ __forceinline__ int sum_word(int lane) {
+    if (lane & 1) return -1;
+    const int v = (lane >> 1) & 3;
+    if (lane & 8) return v == 0 ? 1 : v == 1 ? 3 : v == 3 ? 6 : -1;
+    return v == 0 ? 5 : v == 1 ? 0 : v == 2 ? 2 : 4;
+}
 
 template <int T, int B, bool STORE>
 __device__ __forceinline__ void bwd_tile(int tile, const Ws &ws, const xg_camera *cams,
@@ -630,14 +643,15 @@ __device__ __forceinline__ void bwd_tile(int tile, const Ws &ws, const xg_camera
     wmax = __builtin_amdgcn_readfirstlane(wmax);
 
     float R = 0.0f;   // intensity behind, seen from just after the current Gaussian
-    // the lanes that add a reduced total: entry e of the group, gradient word q
+    // the lane's share of a group's sums: its entry (its row of 16 lanes) and
+    // the gradient word it adds to
     constexpr int G = kBwdGroup;
-    const int lane_e = RedLanes<G>::entry(lane);
-    const int lane_q = RedLanes<G>::word(lane);
-    const bool lane_adds = RedLanes<G>::adds(lane);
+    static_assert(G == kWave / 16, "one row of lanes per entry");
+    const int lane_e = lane >> 4;
+    const int lane_q = sum_word(lane);
     const uint32_t lane_q4 = 4u * (uint32_t)lane_q;
+    const uint32_t lane_bit = lane_q < 0 ? 0u : 1u << lane_e;   // tested against the live entries
     const bool small_rid = ws.n_items < (int64_t)1 << 27;   // 32 B x records below 4 GiB
-    const bool adds_lo = lane_adds && lane_e == 0, adds_hi = lane_adds && lane_e == 1;
     for (int end = bmax; end > 0; end -= B) {
         const int b0 = max(end - B, 0);
         const int cnt = end - b0;
@@ -663,15 +677,19 @@ __device__ __forceinline__ void bwd_tile(int tile, const Ws &ws, const xg_camera
           uint32_t off_n = (iw[3] >> 16) & kOffMask;
           float4 sa_n = slot16(s_a, off_n);
           float4 sb_n = slot16(s_b, off_n);
-          // the 7 gradient terms of G consecutive entries, summed over the
-          // wavefront together; entries that no lane contributes to add zeros
-          // and are left out of the atomics (bit e of live4)
-          float acc[G][7];
-          uint32_t live4 = 0;
-          uint32_t rid = 0;   // Gaussian record of entry lane_e
+          uint32_t live = 0;   // entries of the group that some lane contributes to (bit e)
+          uint32_t eoff = 0, rid = 0;
+          float eux = 0.0f;
+          float acc[G][4];     // gp, gp dy, gp dy^2 and w of the group's entries
 #pragma unroll
           for (int u = 7; u >= 0; --u) {
             const int e = u & (G - 1);
+            // the group's entry of this lane, for the sums after its last entry
+            if (e == G - 1) eoff = list[j0 + (u & ~(G - 1)) + lane_e] & kOffMask;
+            if (e == G - 2) {
+                eux = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(s_a) + eoff);
+                rid = *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(s_rid) + eoff);
+            }
             const uint32_t off = off_n;   // 16 x batch index
             const float4 sa = sa_n;
             const float4 sb = sb_n;
@@ -686,7 +704,7 @@ __device__ __forceinline__ void bwd_tile(int tile, const Ws &ws, const xg_camera
             const bool act = inr && ev.alpha >= amin;
             if (__any(act)) {
                 // Every lane runs the same arithmetic; a lane that is not a
-                // contributor adds exact zeros to the reduction (its alpha
+                // contributor adds exact zeros to the sums (its alpha
                 // taken as 0, its alpha gradient masked) and keeps its
                 // transmittance and R.
                 const float aact = act ? ev.alpha : 0.0f;
@@ -710,8 +728,7 @@ __device__ __forceinline__ void bwd_tile(int tile, const Ws &ws, const xg_camera
                     gT = g * Tj;
                 }
                 const float it = sb.z;
-                float *v = acc[e];
-                v[6] = gT * aact;                              // dL/d intensity
+                const float wi = gT * aact;                    // dL/d intensity
                 const float dR = it - R;
                 const float galpha = gT * dR;                  // dL/d alpha
                 // R after this Gaussian: i alpha + (1 - alpha) R
@@ -719,27 +736,25 @@ __device__ __forceinline__ void bwd_tile(int tile, const Ws &ws, const xg_camera
                 // no alpha gradient through the clamp, nor for a lane that is
                 // not a contributor
                 const float ga = (act && ev.a <= amax) ? galpha : 0.0f;
-                const float gp = ga * ev.a;                    // dL/d power, power = -d^T Q d / 2
-                v[5] = gp;                                     // opacity x dL/d opacity (a = o G)
-                // moments of gp over the pixel offsets d = pixel - u; the inverse
-                // covariance is applied once per (view, Gaussian)
-                v[0] = gp * ev.dx;
-                v[1] = gp * ev.dy;
-                v[2] = v[0] * ev.dx;
-                v[3] = v[0] * ev.dy;
-                v[4] = v[1] * ev.dy;
-                if (lane_e == e) rid = *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(s_rid) + off);
-                live4 |= 1u << e;
+                // dL/d power, power = -d^T Q d / 2.  Its sum is the opacity
+                // times dL/d opacity (a = o G); its moments over the pixel
+                // offsets d = pixel - u give the gradients of u and Sigma''
+                // (the inverse covariance is applied once per (view, Gaussian))
+                const float gp = ga * ev.a;
+                acc[e][0] = gp;
+                acc[e][1] = gp * ev.dy;
+                acc[e][2] = acc[e][1] * ev.dy;
+                acc[e][3] = wi;
+                live |= 1u << e;
             } else {
 #pragma unroll
-                for (int q = 0; q < 7; ++q) acc[e][q] = 0.0f;
+                for (int q = 0; q < 4; ++q) acc[e][q] = 0.0f;
             }
-            if (e == 0 && live4 != 0) {
-                const float x = wave_reduce_group(acc);
-                // the adding lanes of the live entries (a wavefront-uniform
-                // choice per half: no per-lane test of live4)
-                const bool l0 = live4 & 1u, l1 = live4 & 2u;
-                if ((l0 && adds_lo) || (l1 && adds_hi)) {
+            if (e == 0 && live != 0) {
+                float c2[2];
+                row_sums(acc, lane, c2);
+                const float x = column_sums(c2, pxr - eux, lane);
+                if (live & lane_bit) {
                     if (small_rid) {   // 32-bit byte offset from the array base
                         atomicAdd(reinterpret_cast<float *>(reinterpret_cast<char *>(ws.grad2d) + (rid << 5 | lane_q4)), x);
                     } else {
@@ -747,15 +762,17 @@ __device__ __forceinline__ void bwd_tile(int tile, const Ws &ws, const xg_camera
                         __asm__ volatile("" ::: "memory");   // keeps the two atomics apart
                     }
                 }
-                live4 = 0;
+                live = 0;
             }
           }
         }
     }
 }
 
+// (64 registers for the plain variants of several wavefronts: 8 wavefronts
+// per SIMD, and two workgroups per CU of 32 x 32 tiles)
 template <int T, int B, bool PERSIST, bool STORE>
-__global__ __launch_bounds__(T * T) void k_render_bwd(Ws ws, const xg_camera *cams, Params p,
+__global__ __launch_bounds__(T * T, T > 8 && !PERSIST && !STORE ? 8 : 2) void k_render_bwd(Ws ws, const xg_camera *cams, Params p,
                                                       const float *dl_dimage, const float *final_t,
                                                       const int32_t *n_contrib, TStore ts) {
     __shared__ BlendLds<T, B> sh;
