@@ -75,7 +75,7 @@ struct Plan {
     size_t icounts, scan_tmp, ikeys[2], ivals[2], ptile[2], pval[2], ghist, vhist, bin_cnt, bin_ptot,
         bin_pstart, lookback[2], tile_order, xcd_order, blend_order, ssim, entry_mask;
     int64_t total_px, total_tiles, n_items;
-    int32_t item_blocks, pair_blocks, tile_bits, pair_passes, pair_gbits, bin_tiles, bin_ppv;
+    int32_t item_blocks, pair_blocks, tile_bits, pair_passes, pair_gbits, bin_tiles, bin_ppv, bin_items;
 };
 
 int bits_of(int64_t v) { return v <= 0 ? 0 : 64 - __builtin_clzll((unsigned long long)v); }
@@ -95,7 +95,18 @@ xg_status make_plan(const xg_frame *f, bool need_ws, Plan &P) {
         if (t > max_view_tiles) max_view_tiles = t;
     }
     P.bin_tiles = max_view_tiles <= kBinMaxTiles ? (int32_t)max_view_tiles : 0;
-    P.bin_ppv = (int32_t)(((int64_t)f->n + kBinItems - 1) / kBinItems);
+    // Partitions as small as still leave every one its own resident ranking
+    // workgroup: a frame of few items is otherwise ranked by a handful of
+    // workgroups, window after window.  Partitions of 2048 -> by this rule,
+    // count + rank: 43k items, one view of 512 x 512: 68 -> 16 us (256 items);
+    // 200k, one view: 40 -> 20 us (512).  Beyond one round of workgroups the
+    // longer column scans and the fixed cost of a partition take over:
+    // 1024 items at 16 M items cost 80 us more than 2048.
+    P.bin_items = kBinItems;
+    while (P.bin_items > kBinItemsMin &&
+           f->n_views * (((int64_t)f->n + P.bin_items / 2 - 1) / (P.bin_items / 2)) <= kBinResident)
+        P.bin_items /= 2;
+    P.bin_ppv = (int32_t)(((int64_t)f->n + P.bin_items - 1) / P.bin_items);
     P.tile_bits = bits_of(P.total_tiles - 1);
     P.pair_passes = (P.tile_bits + kRadixBits - 1) / kRadixBits;
     // one word per pair when tile id and Gaussian index fit 32 bits together
@@ -169,6 +180,7 @@ Ws resolve(const xg_frame *f, const Plan &P) {
     w.bin_pstart = (uint32_t *)(b + P.bin_pstart);
     w.bin_tiles = P.bin_tiles;
     w.bin_ppv = P.bin_ppv;
+    w.bin_items = P.bin_items;
     w.pctr = w.ghist + kMaxPasses * kRadix * kGhStride;
     w.lookback[0] = (uint64_t *)(b + P.lookback[0]);
     w.lookback[1] = (uint64_t *)(b + P.lookback[1]);

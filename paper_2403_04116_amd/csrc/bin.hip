@@ -8,11 +8,11 @@
 // therefore a stable counting sort of each view's pairs by view-local tile
 // id, whose digit range (the view's tiles, at most kBinMaxTiles) is small
 // enough to count in LDS:
-//   1. k_bin_count: per partition (kBinItems consecutive items of one
+//   1. k_bin_count: per partition (ws.bin_items consecutive items of one
 //      view), the number of pairs of each tile (LDS atomics over the items'
 //      tile rectangles) -> one row of bin_cnt;
 //   2. k_bin_columns: down each (view, tile) column of bin_cnt, the
-//      exclusive scan over the view's partitions (four segments in parallel),
+//      exclusive scan over the view's partitions (segments in parallel),
 //      and the tile's total;
 //   3. k_bin_starts: per view, the exclusive scan of the tile totals from
 //      the view's first pair slot -> the tile ranges [start, end);
@@ -42,8 +42,8 @@ __device__ __forceinline__ BinPart bin_part(const Ws &ws, const xg_camera *cams,
     b.view = part / ws.bin_ppv;
     b.q = part - b.view * ws.bin_ppv;
     const int64_t vbase = (int64_t)b.view * ws.n;
-    b.j0 = vbase + (int64_t)b.q * kBinItems;
-    b.j1 = min(b.j0 + kBinItems, vbase + ws.n);
+    b.j0 = vbase + (int64_t)b.q * ws.bin_items;
+    b.j1 = min(b.j0 + ws.bin_items, vbase + ws.n);
     const xg_camera &c = cams[b.view];
     b.tiles_x = (c.width + tile - 1) / tile;
     b.tiles = b.tiles_x * ((c.height + tile - 1) / tile);
@@ -97,11 +97,11 @@ __global__ __launch_bounds__(kCountThreads) void k_bin_count(Ws ws, const xg_cam
 // Exclusive scan down each (view, local tile) column of bin_cnt over the
 // view's partitions, rewritten in place; the column total goes to the
 // tile's range start word until k_bin_starts replaces it.  A workgroup
-// takes 64 columns; its four wavefronts split each column's partitions into
-// four consecutive segments: each sums its segment, the segment totals are
+// takes 64 columns; its wavefronts split each column's partitions into
+// kColSegs consecutive segments: each sums its segment, the segment totals are
 // scanned through LDS, and each rewrites its segment from its offset.
 constexpr int kColTiles = 64;
-constexpr int kColSegs = 4;
+constexpr int kColSegs = 8;
 constexpr int kColThreads = kColTiles * kColSegs;
 
 __global__ __launch_bounds__(kColThreads) void k_bin_columns(Ws ws, const xg_camera *cams, int tile,
@@ -244,14 +244,15 @@ __global__ __launch_bounds__(kStartThreads) void k_bin_starts(Ws ws, const xg_ca
 // wavefront scan of the tile totals), so that the stores of a row write
 // runs of consecutive list entries.
 // (16 wavefronts: at most 64 registers, so that two workgroups share a CU)
-template <int LT, int NW>
+// MI = items per thread: the partitions hold at most MI NT items.
+template <int LT, int NW, int MI>
 __global__ __launch_bounds__(NW * kWave, NW == 16 ? 8 : 2) void k_bin_scatter(Ws ws, const xg_camera *cams,
                                                                               int tile) {
     constexpr int NT = NW * kWave;
     constexpr int LB = LT <= 1024 ? 10 : 12;
     constexpr int kRows = kBinWindow / NT;         // rows of 64 slots per wavefront
-    constexpr int kMyItems = kBinItems / NT;       // items per thread
-    static_assert(LT <= (1 << LB) && kBinWindow % NT == 0 && kBinItems % NT == 0, "shape");
+    constexpr int kMyItems = MI;
+    static_assert(LT <= (1 << LB) && kBinWindow % NT == 0, "shape");
     static_assert(kBinWindow <= 65535, "window offsets and counts fit 16 bits");
     __shared__ uint32_t h16[NW][LT / 2];
     __shared__ uint32_t base[LT];
@@ -490,7 +491,9 @@ __global__ __launch_bounds__(NW * kWave, NW == 16 ? 8 : 2) void k_bin_scatter(Ws
 }  // namespace
 
 hipError_t launch_bin_lists(const Ws &ws, const xg_camera *cams, const Params &p, hipStream_t s) {
-    if (ws.bin_tiles <= 0 || ws.bin_tiles > kBinMaxTiles || ws.bin_ppv <= 0) return hipErrorInvalidValue;
+    if (ws.bin_tiles <= 0 || ws.bin_tiles > kBinMaxTiles || ws.bin_ppv <= 0 || ws.bin_items <= 0 ||
+        ws.bin_items > kBinItems)
+        return hipErrorInvalidValue;
     const int64_t parts = (int64_t)ws.n_views * ws.bin_ppv;
     if (parts > 0x7fffffff) return hipErrorInvalidValue;
     const unsigned np = (unsigned)parts;
@@ -500,10 +503,18 @@ hipError_t launch_bin_lists(const Ws &ws, const xg_camera *cams, const Params &p
                        cams, p.tile, chunks);
     hipLaunchKernelGGL(k_bin_starts, dim3((unsigned)ws.n_views), dim3(kStartThreads), 0, s, ws, cams, p.tile);
     // kXcds extra workgroups write the blend launches' tile order
-    if (ws.bin_tiles <= 1024)
-        hipLaunchKernelGGL((k_bin_scatter<1024, 16>), dim3(np + kXcds), dim3(16 * kWave), 0, s, ws, cams, p.tile);
-    else
-        hipLaunchKernelGGL((k_bin_scatter<4096, 8>), dim3(np + kXcds), dim3(8 * kWave), 0, s, ws, cams, p.tile);
+    const dim3 grid(np + kXcds);
+    if (ws.bin_tiles <= 1024) {
+        if (ws.bin_items > 1024)
+            hipLaunchKernelGGL((k_bin_scatter<1024, 16, 2>), grid, dim3(16 * kWave), 0, s, ws, cams, p.tile);
+        else
+            hipLaunchKernelGGL((k_bin_scatter<1024, 16, 1>), grid, dim3(16 * kWave), 0, s, ws, cams, p.tile);
+    } else {
+        if (ws.bin_items > 512)
+            hipLaunchKernelGGL((k_bin_scatter<4096, 8, 4>), grid, dim3(8 * kWave), 0, s, ws, cams, p.tile);
+        else
+            hipLaunchKernelGGL((k_bin_scatter<4096, 8, 1>), grid, dim3(8 * kWave), 0, s, ws, cams, p.tile);
+    }
     return hipGetLastError();
 }
 

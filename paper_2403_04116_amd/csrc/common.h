@@ -120,10 +120,11 @@ struct Ws {
     uint32_t pair_gmask;
     const uint32_t *pair_vals;
     // Tile lists by counting (bin_tiles > 0): the row length of bin_cnt (the
-    // most tiles of any view) and the partitions of kBinItems items per view.
+    // most tiles of any view), and per view the partitions of bin_items items.
     // bin_tiles = 0: emission and the radix sort of the pairs by tile.
     int32_t bin_tiles;
     int32_t bin_ppv;
+    int32_t bin_items;
 };
 
 // Scalar constants of one rendering.
@@ -195,10 +196,12 @@ __device__ __forceinline__ uint64_t match_peers(uint32_t d, bool valid) {
     return (uint64_t)lo | ((uint64_t)hi << 32);
 }
 
-// Tile lists by counting: items per partition (all of one view), pairs per
-// LDS window of the ranking kernel, and the most tiles a view may have on
+// Tile lists by counting: most items per partition (all of one view), pairs
+// per LDS window of the ranking kernel, and the most tiles a view may have on
 // this path (larger views use emission and the radix sort of the pairs).
 constexpr int kBinItems = 2048;
+constexpr int kBinItemsMin = 256;
+constexpr int kBinResident = 512;   // ranking workgroups the device holds at once (two per CU)
 constexpr int kBinWindow = 4096;
 constexpr int kBinMaxTiles = 4096;
 
