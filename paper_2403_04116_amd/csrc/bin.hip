@@ -497,11 +497,13 @@ hipError_t launch_bin_lists(const Ws &ws, const xg_camera *cams, const Params &p
     const int64_t parts = (int64_t)ws.n_views * ws.bin_ppv;
     if (parts > 0x7fffffff) return hipErrorInvalidValue;
     const unsigned np = (unsigned)parts;
-    hipLaunchKernelGGL(k_bin_count, dim3(np), dim3(kCountThreads), 0, s, ws, cams, p.tile);
-    const int chunks = (ws.bin_tiles + kColTiles - 1) / kColTiles;
-    hipLaunchKernelGGL(k_bin_columns, dim3((unsigned)(ws.n_views * chunks)), dim3(kColThreads), 0, s, ws,
-                       cams, p.tile, chunks);
-    hipLaunchKernelGGL(k_bin_starts, dim3((unsigned)ws.n_views), dim3(kStartThreads), 0, s, ws, cams, p.tile);
+    if (ws.view_sort != ViewSort::kLists) {   // else counted by the item sort's launch
+        hipLaunchKernelGGL(k_bin_count, dim3(np), dim3(kCountThreads), 0, s, ws, cams, p.tile);
+        const int chunks = (ws.bin_tiles + kColTiles - 1) / kColTiles;
+        hipLaunchKernelGGL(k_bin_columns, dim3((unsigned)(ws.n_views * chunks)), dim3(kColThreads), 0, s, ws,
+                           cams, p.tile, chunks);
+        hipLaunchKernelGGL(k_bin_starts, dim3((unsigned)ws.n_views), dim3(kStartThreads), 0, s, ws, cams, p.tile);
+    }
     // kXcds extra workgroups write the blend launches' tile order
     const dim3 grid(np + kXcds);
     if (ws.bin_tiles <= 1024) {

@@ -72,6 +72,22 @@ __device__ __forceinline__ int ordered_tile(const int32_t *order, int b, int n) 
     return (unsigned)t < (unsigned)n ? t : i;
 }
 
+// How the items of a frame are sorted: by the radix passes over all views,
+// or each view by one workgroup, with or without the counting of the tile
+// lists in the same launch.
+enum class ViewSort : int32_t { kNone, kItems, kLists };
+constexpr int kViewSortThreads = 1024;
+constexpr int kViewSortItems = 8;                                   // most items per thread
+constexpr int kViewSortMax = kViewSortThreads * kViewSortItems;
+constexpr int kViewListsItems = 4;                                  // the same where it counts the lists
+constexpr int kViewSortParts = 64;                                  // most list partitions of a view
+constexpr int64_t kViewListsMax = 65536;                            // most items of a frame counted in the launch
+// LDS words of the one-workgroup sort: keys, 16-bit item numbers, per
+// wavefront a digit histogram and a table of 64-bit lane masks
+constexpr int view_sort_words(int items) {
+    return kViewSortThreads * items * 3 / 2 + kViewSortThreads / kWave * 256 * 3;
+}
+
 // Device view of a workspace, resolved on the host from the layout.
 struct Ws {
     WsHeader *hdr;
@@ -125,6 +141,7 @@ struct Ws {
     int32_t bin_tiles;
     int32_t bin_ppv;
     int32_t bin_items;
+    ViewSort view_sort;
 };
 
 // Scalar constants of one rendering.
@@ -229,7 +246,7 @@ hipError_t launch_preprocess(const Ws &ws, const xg_gaussians &g, const xg_camer
                              const Params &p, hipStream_t s);
 hipError_t launch_scan(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp,
                        int32_t *total, int32_t *status, int64_t cap, hipStream_t s);
-hipError_t launch_sort_items(const Ws &ws, hipStream_t s);
+hipError_t launch_sort_items(const Ws &ws, const xg_camera *cams, const Params &p, hipStream_t s);
 hipError_t launch_emit(const Ws &ws, const xg_camera *cams, const Params &p, hipStream_t s);
 hipError_t launch_sort_pairs(const Ws &ws, hipStream_t s);
 hipError_t launch_ranges(const Ws &ws, bool cleared, hipStream_t s);  // cleared: by the pair sort
