@@ -72,11 +72,12 @@ xg_status check_frame(const xg_frame *f, bool need_ws, int64_t *tot_px, int64_t 
 
 struct Plan {
     xg_ws_layout lay;
-    size_t icounts, scan_tmp, ikeys[2], ivals[2], ptile[2], pval[2], ghist, vhist, bin_cnt, bin_ptot,
+    size_t icounts, scan_tmp, ikeys[2], ivals[2], ptile[2], pval[2], ghist, vhist, vctr, bin_cnt, bin_ptot,
         bin_pstart, lookback[2], tile_order, xcd_order, blend_order, ssim, entry_mask;
     int64_t total_px, total_tiles, n_items;
     int32_t item_blocks, pair_blocks, tile_bits, pair_passes, pair_gbits, bin_tiles, bin_ppv, bin_items;
     ViewSort view_sort;
+    bool sort_fold;
 };
 
 int bits_of(int64_t v) { return v <= 0 ? 0 : 64 - __builtin_clzll((unsigned long long)v); }
@@ -128,6 +129,10 @@ xg_status make_plan(const xg_frame *f, bool need_ws, Plan &P) {
         }
     }
     P.bin_ppv = (int32_t)(((int64_t)f->n + P.bin_items - 1) / P.bin_items);
+    // the radix passes of the items without their clearing launch (the
+    // launch that counts the lists leaves the cleared words zero again)
+    P.sort_fold = P.view_sort == ViewSort::kNone && f->n > kViewSortMax && P.bin_tiles > 0 &&
+                  (ni + kPreThreads - 1) / kPreThreads <= kFoldParts;
     P.tile_bits = bits_of(P.total_tiles - 1);
     P.pair_passes = (P.tile_bits + kRadixBits - 1) / kRadixBits;
     // one word per pair when tile id and Gaussian index fit 32 bits together
@@ -160,6 +165,7 @@ xg_status make_plan(const xg_frame *f, bool need_ws, Plan &P) {
     }
     P.ghist = o;              o = align_up(o + 4 * (size_t)kSortCtlWords);
     P.vhist = o;              o = align_up(o + 4 * (size_t)f->n_views * kMaxPasses * kRadix);
+    P.vctr = o;               o = align_up(o + 4 * (size_t)f->n_views * kMaxPasses * kGhStride);
     P.bin_cnt = o;            o = align_up(o + 4 * (size_t)f->n_views * P.bin_ppv * P.bin_tiles);
     P.bin_ptot = o;           o = align_up(o + 4 * (size_t)f->n_views * P.bin_ppv);
     P.bin_pstart = o;         o = align_up(o + 4 * (size_t)f->n_views * P.bin_ppv);
@@ -196,6 +202,8 @@ Ws resolve(const xg_frame *f, const Plan &P) {
     }
     w.ghist = (uint32_t *)(b + P.ghist);
     w.vhist = (uint32_t *)(b + P.vhist);
+    w.vctr = (uint32_t *)(b + P.vctr);
+    w.sort_fold = P.sort_fold;
     w.bin_cnt = (uint32_t *)(b + P.bin_cnt);
     w.bin_ptot = (uint32_t *)(b + P.bin_ptot);
     w.bin_pstart = (uint32_t *)(b + P.bin_pstart);

@@ -57,6 +57,11 @@ static_assert(kBinItems % kCountThreads == 0, "whole items per thread");
 __global__ __launch_bounds__(kCountThreads) void k_bin_count(Ws ws, const xg_camera *cams, int tile) {
     __shared__ uint32_t cnt[kBinMaxTiles];
     const BinPart b = bin_part(ws, cams, tile, blockIdx.x);
+    // the item sort is over: leave its digit totals and counters zero
+    if (ws.sort_fold)
+        for (int64_t i = (int64_t)blockIdx.x * kCountThreads + threadIdx.x; i < item_sort_zeros(ws);
+             i += (int64_t)gridDim.x * kCountThreads)
+            zero_item_sort(ws, i);
     for (int t = threadIdx.x; t < b.tiles; t += kCountThreads) cnt[t] = 0;
     __syncthreads();
     const int sel = ws.hdr->item_sel & 1;
@@ -169,7 +174,7 @@ __global__ __launch_bounds__(kColThreads) void k_bin_columns(Ws ws, const xg_cam
 constexpr int kStartThreads = 1024;
 
 __global__ __launch_bounds__(kStartThreads) void k_bin_starts(Ws ws, const xg_camera *cams, int tile) {
-    __shared__ uint32_t lds[kStartThreads / kWave + 1];
+    __shared__ alignas(16) uint32_t lds[kScanLds];
     __shared__ uint64_t s_sum[2][kStartThreads / kWave];
     const int v = blockIdx.x;
     const xg_camera &c = cams[v];
@@ -261,7 +266,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 16 ? 8 : 2) void k_bin_scatter(Ws
     // the window's slots in tile order (slot of each window position), and
     // each tile's first window position (two 16-bit starts per word)
     __shared__ uint16_t s_perm[kBinWindow];
-    __shared__ uint32_t s_lst[LT / 2];
+    __shared__ alignas(16) uint32_t s_lst[LT / 2];
     __shared__ uint32_t s_alloc;
     // ranking: per wavefront, a 64-bit lane mask for each value of a tile's
     // low kHashBits bits (zero between rows)
@@ -272,7 +277,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 16 ? 8 : 2) void k_bin_scatter(Ws
     // ranges are final; every status, since the blends read it even when
     // the lists are empty), in slots the partitions leave idle
     if ((int)blockIdx.x < kXcds) {
-        static_assert(NW * (LT / 2) >= kOrderGroups && LT >= kOrderBuckets && LT / 2 > NW, "scratch of the order");
+        static_assert(NW * (LT / 2) >= kOrderGroups && LT >= kOrderBuckets && LT / 2 >= kScanLds, "scratch of the order");
         xcd_order_block(ws, blockIdx.x, base, s_lst, &h16[0][0]);
         return;
     }
@@ -363,17 +368,22 @@ __global__ __launch_bounds__(NW * kWave, NW == 16 ? 8 : 2) void k_bin_scatter(Ws
             const uint32_t cnt = i_cy[k] & 0xffffu;
             const uint32_t a = max(i_off[k], w0), e = min(i_off[k] + cnt, w1);
             if (cnt == 0 || a >= e) continue;
-            const int tx0 = (int)(i_x[k] & 0xffffu), tx1 = (int)(i_x[k] >> 16);
-            const uint32_t rw = (uint32_t)(tx1 - tx0 + 1);
-            const uint32_t m = a - i_off[k];
-            int ty = (int)(i_cy[k] >> 16) + (int)(m / rw);
-            int tx = tx0 + (int)(m % rw);
-            for (uint32_t s = a; s < e; ++s) {
-                s_lt[s - w0] = (uint16_t)(ty * b.tiles_x + tx);
-                s_gi[s - w0] = i_gi[k];
-                if (++tx > tx1) {
-                    tx = tx0;
-                    ++ty;
+            const uint32_t tx0 = i_x[k] & 0xffffu, rw = (i_x[k] >> 16) - tx0 + 1u;
+            uint32_t lt = (i_cy[k] >> 16) * (uint32_t)b.tiles_x + tx0;
+            uint32_t left = rw;   // pairs left in the row
+            // (only an item begun in an earlier window skips whole rows)
+            uint32_t skip = a - i_off[k];
+            for (; skip >= rw; skip -= rw) lt += (uint32_t)b.tiles_x;
+            lt += skip;
+            left -= skip;
+            const uint32_t step = (uint32_t)b.tiles_x - rw;   // from a row's end to the next row
+#pragma unroll 1
+            for (uint32_t s = a - w0; s < e - w0; ++s) {
+                s_lt[s] = (uint16_t)lt++;
+                s_gi[s] = i_gi[k];
+                if (--left == 0) {
+                    left = rw;
+                    lt += step;
                 }
             }
         }
@@ -394,14 +404,14 @@ __global__ __launch_bounds__(NW * kWave, NW == 16 ? 8 : 2) void k_bin_scatter(Ws
             const uint64_t same_low = *slotp;
             *slotp = 0ull;
             const uint64_t peers = valid ? same_low & match_peers<LB - kHashBits>(t >> kHashBits, valid) : 0ull;
-            const int leader = __ffsll((unsigned long long)peers) - 1;
-            uint32_t old = 0;
-            if (valid && lane == leader) {
-                const uint32_t sh = 16u * (t & 1u);
-                old = (atomicAdd(&h16[w][t >> 1], (uint32_t)__popcll(peers) << sh) >> sh) & 0xffffu;
-            }
-            old = (uint32_t)__shfl((int)old, leader < 0 ? 0 : leader, kWave);
-            rt[r] = (old + (uint32_t)__popcll(peers & lt_mask)) | (t << 16);
+            // every lane reads its tile's count, then the first lane of each
+            // tile adds the row's (two tiles share a word: an atomic, whose
+            // result nothing waits for)
+            const uint32_t below = (uint32_t)__popcll(peers & lt_mask);
+            const uint32_t sh = 16u * (t & 1u);
+            const uint32_t old = (h16[w][t >> 1] >> sh) & 0xffffu;
+            if (valid && below == 0) atomicAdd(&h16[w][t >> 1], (uint32_t)__popcll(peers) << sh);
+            rt[r] = (old + below) | (t << 16);
         }
         __syncthreads();
         // prefix over the wavefronts, two tiles (one word) per step; then each
@@ -425,16 +435,11 @@ __global__ __launch_bounds__(NW * kWave, NW == 16 ? 8 : 2) void k_bin_scatter(Ws
             adv[k] = run;
             const uint32_t lo = run & 0xffffu;
             const uint32_t tot = lo + (run >> 16);
-            uint32_t incl = tot;
-#pragma unroll
-            for (int d = 1; d < kWave; d <<= 1) {
-                const uint32_t up = (uint32_t)__shfl_up((int)incl, d, kWave);
-                if (lane >= d) incl += up;
-            }
-            const uint32_t wsum = (uint32_t)__shfl((int)incl, kWave - 1, kWave);
+            const uint32_t incl = wave_incl_scan(tot);
+            const uint32_t wsum = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
             uint32_t wbase = 0;
             if (lane == 0 && wsum) wbase = atomicAdd(&s_alloc, wsum);
-            wbase = (uint32_t)__shfl((int)wbase, 0, kWave);
+            wbase = (uint32_t)__builtin_amdgcn_readfirstlane((int)wbase);
             const uint32_t st = wbase + incl - tot;
             if (tw < LT / 2 && tot) s_lst[tw] = st | ((st + lo) << 16);
         }

@@ -102,6 +102,8 @@ struct Ws {
     uint32_t *pval[2];     // pair sort values (Gaussian index)
     uint32_t *ghist;       // radix sort: digit histograms [kMaxPasses][kRadix], one 128-byte line each
     uint32_t *vhist;       // item sort (within each view): digit totals [view][kMaxPasses][kRadix]
+    uint32_t *vctr;        // item sort: partition counters [view][kMaxPasses], one 128-byte line each
+    bool sort_fold;        // item sort: its histogram launch folds the depth partials (no clearing launch)
     uint32_t *bin_cnt;     // tile lists by counting: [view][partition][local tile] pair counts,
                            // then their exclusive scan down each column
     uint32_t *bin_ptot;    // tile lists by counting: pairs of each [view][partition]
@@ -241,6 +243,24 @@ constexpr int kMaxPasses = 4;                            // 32 depth bits, 8 at 
 constexpr int kGhStride = 32;   // words between histogram bins (spreads their atomics over channels)
 constexpr int kSortCtlWords = (kMaxPasses * kRadix + kMaxPasses) * kGhStride;
 
+// Preprocess workgroups (depth partials) up to which the item sort's
+// histogram launch folds them in every workgroup, instead of a clearing
+// launch that folds a share in each: 8192 pairs are 8 loads a thread; at
+// 62 500 (16 M items) the launch is the cheaper one.
+constexpr int64_t kFoldParts = 8192;
+
+// The item sort's words that are zero before its histogram launch.
+__device__ __forceinline__ int64_t item_sort_zeros(const Ws &ws) {
+    return (int64_t)ws.n_views * kMaxPasses * (kRadix + 1);
+}
+__device__ __forceinline__ void zero_item_sort(const Ws &ws, int64_t i) {
+    const int64_t bins = (int64_t)ws.n_views * kMaxPasses * kRadix;
+    if (i < bins)
+        ws.vhist[i] = 0;
+    else
+        ws.vctr[(i - bins) * kGhStride] = 0;
+}
+
 // ---- launchers (one translation unit per stage) --------------------------
 hipError_t launch_preprocess(const Ws &ws, const xg_gaussians &g, const xg_camera *cams,
                              const Params &p, hipStream_t s);
@@ -309,38 +329,64 @@ hipError_t launch_adam(const xg_params &p, const xg_grads &g, float *m, float *v
 // ---- device helpers ------------------------------------------------------
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
-// Wave-wide inclusive prefix sum of a uint32 (64 lanes).
+// Wave-wide inclusive prefix sum of a uint32 (64 lanes, all active): within
+// each row of 16 by DPP shifts, then the rows' last lanes broadcast onward
+// (six VALU instructions; as LDS permutes each step costs an LDS round trip).
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
-    const int l = lane_id();
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        uint32_t t = __shfl_up(v, o, kWave);
-        if (l >= o) v += t;
-    }
+#define XG_SCAN_STEP(ctrl, rows) v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, rows, 0xf, false)
+    XG_SCAN_STEP(0x111, 0xf);   // row_shr:1
+    XG_SCAN_STEP(0x112, 0xf);   // row_shr:2
+    XG_SCAN_STEP(0x114, 0xf);   // row_shr:4
+    XG_SCAN_STEP(0x118, 0xf);   // row_shr:8
+    XG_SCAN_STEP(0x142, 0xa);   // row_bcast:15 into rows 1 and 3
+    XG_SCAN_STEP(0x143, 0xc);   // row_bcast:31 into rows 2 and 3
+#undef XG_SCAN_STEP
     return v;
 }
 
-// Block-wide exclusive prefix sum over blockDim.x threads (multiple of 64,
-// at most 1024).  `lds` must hold blockDim.x / 64 + 1 words.  Returns the
-// exclusive prefix of v; *total receives the block sum.  Contains barriers.
-__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *lds, uint32_t *total) {
-    const int l = lane_id();
+// Block-wide exclusive prefix sums of Q values at once, over blockDim.x
+// threads (multiple of 64, at most 1024).  `lds` must hold Q rows of
+// kScanLds words, 16-byte aligned.  v[q] becomes the exclusive prefix,
+// total[q] the block sum.  Two barriers: every thread adds up the wavefront
+// totals itself.
+constexpr int kScanLds = 1024 / kWave;
+template <int Q>
+__device__ __forceinline__ void block_excl_scans(uint32_t (&v)[Q], uint32_t *lds, uint32_t (&total)[Q]) {
     const int w = threadIdx.x / kWave;
     const int nw = blockDim.x / kWave;
-    uint32_t inc = wave_incl_scan(v);
-    if (l == kWave - 1) lds[w] = inc;
-    __syncthreads();
-    if (w == 0) {
-        uint32_t x = (l < nw) ? lds[l] : 0u;
-        uint32_t xi = wave_incl_scan(x);
-        if (l < nw) lds[l] = xi - x;
-        if (l == nw - 1) lds[nw] = xi;
+    uint32_t inc[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        inc[q] = wave_incl_scan(v[q]);
+        if (lane_id() == kWave - 1) lds[q * kScanLds + w] = inc[q];
     }
     __syncthreads();
-    uint32_t res = lds[w] + inc - v;
-    *total = lds[nw];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        uint32_t before = 0, sum = 0;
+        const uint4 *rows = reinterpret_cast<const uint4 *>(lds + q * kScanLds);
+#pragma unroll
+        for (int k4 = 0; k4 < kScanLds / 4; ++k4) {
+            const uint4 r = rows[k4];   // words past the block's wavefronts: never written, not added
+            const uint32_t x[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                before += 4 * k4 + k < w ? x[k] : 0u;
+                sum += 4 * k4 + k < nw ? x[k] : 0u;
+            }
+        }
+        v[q] = before + inc[q] - v[q];
+        total[q] = sum;
+    }
     __syncthreads();
-    return res;
+}
+
+// The same for one value; `lds` holds kScanLds words.
+__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *lds, uint32_t *total) {
+    uint32_t a[1] = {v}, t[1];
+    block_excl_scans<1>(a, lds, t);
+    *total = t[0];
+    return a[0];
 }
 
 // Work-order buckets of list lengths: eight per octave, longest first.
@@ -375,7 +421,7 @@ struct TileDeal {
 // Writes the cnt tiles tile_of(j) longest list first to out (buckets of an
 // eighth of an octave; the order inside a bucket is arbitrary).  The
 // workgroup has at least kOrderBuckets threads; hist: kOrderBuckets words
-// of LDS; scan_lds: blockDim.x / 64 + 1 words.  Contains barriers.
+// of LDS; scan_lds: kScanLds words.  Contains barriers.
 template <class TileOf>
 __device__ __forceinline__ void order_tiles(const Ws &ws, int cnt, TileOf tile_of, int32_t *out, uint32_t *hist,
                                             uint32_t *scan_lds) {

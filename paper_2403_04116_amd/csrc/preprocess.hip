@@ -197,6 +197,9 @@ __global__ __launch_bounds__(kPreThreads) void k_preprocess(Ws ws, xg_gaussians 
         ws.hdr->depth_min = 0xffffffffu;
         ws.hdr->depth_max = 0u;
     }
+    // the item sort's digit totals and counters (a view has more items than
+    // that wherever the sort relies on it)
+    if (ws.sort_fold && idx < item_sort_zeros(ws)) zero_item_sort(ws, idx);
     // The workgroup's records (and 2-D gradient accumulators) form one
     // contiguous range; they are staged in LDS (16-byte part k of record t
     // at s_rec[k][t]: conflict-free) and written with whole cache lines.

@@ -13,7 +13,7 @@ namespace {
 
 __global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const uint32_t *in, int64_t n,
                                                               uint32_t *sums) {
-    __shared__ uint32_t lds[kScanThreads / kWave + 1];
+    __shared__ alignas(16) uint32_t lds[kScanLds];
     const int64_t base = (int64_t)blockIdx.x * kScanBlock;
     uint32_t acc = 0;
 #pragma unroll
@@ -30,7 +30,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const uint32_t *in
 // raises XG_ECAPACITY when it exceeds `cap`.
 __global__ __launch_bounds__(1024) void k_scan_top(uint32_t *sums, int64_t nb, int32_t *total,
                                                    int32_t *status, int64_t cap) {
-    __shared__ uint32_t lds[1024 / kWave + 1];
+    __shared__ alignas(16) uint32_t lds[kScanLds];
     uint64_t carry = 0;
     for (int64_t c = 0; c < nb; c += blockDim.x) {
         const int64_t j = c + threadIdx.x;
@@ -56,7 +56,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(const uint32_t *in, 
                                                             int64_t n, const uint32_t *sums,
                                                             int32_t *total, int32_t *status,
                                                             int64_t cap) {
-    __shared__ uint32_t lds[kScanThreads / kWave + 1];
+    __shared__ alignas(16) uint32_t lds[kScanLds];
     __shared__ uint32_t tile[kScanBlock];
     __shared__ uint64_t part[kScanThreads / kWave];
     const int64_t base = (int64_t)blockIdx.x * kScanBlock;

@@ -200,6 +200,20 @@ __device__ __forceinline__ uint32_t *digit_bin(const Ws &ws, int64_t segment, in
         return ws.ghist + (pass * kRadix + d) * kGhStride;
 }
 
+// The counter that hands out a pass's partitions: one for the unsegmented
+// sorts, one per view for the items (a line each), so that few workgroups
+// queue on a word.
+template <class S>
+__device__ __forceinline__ uint32_t *part_counter(const Ws &ws, int64_t segment, int pass) {
+    return S::kSegmented ? ws.vctr + (segment * kMaxPasses + pass) * kGhStride : ws.pctr + pass * kGhStride;
+}
+
+// Words of the item sort that are zero between frames where its histogram
+// launch folds the depth partials (ws.sort_fold): the digit totals of every
+// view and the partition counters.  The preprocess zeroes them, and the
+// launch after the sort again, so that a second list build of the same
+// preprocess finds them zero too.
+
 // Zeroes the digit histograms, partition counters and the first pass's
 // look-back words of one sort.  The item sort's (depth_part set) also
 // resets the frame header (workgroup 0) and folds the preprocess's depth
@@ -217,7 +231,7 @@ __global__ __launch_bounds__(256) void k_sort_prep(Ws ws, const uint32_t *depth_
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = i0; i < kSortCtlWords; i += stride) ws.ghist[i] = 0;
     if (S::kSegmented)
-        for (int64_t i = i0; i < (int64_t)ws.n_views * kMaxPasses * kRadix; i += stride) ws.vhist[i] = 0;
+        for (int64_t i = i0; i < item_sort_zeros(ws); i += stride) zero_item_sort(ws, i);
     for (int64_t i = i0; i < parts * kRadix; i += stride) ws.lookback[0][i] = 0;
     if (S::kClearRanges)
         for (int64_t i = i0; i < 2 * ws.total_tiles; i += stride) ws.ranges[i] = 0;
@@ -232,12 +246,53 @@ __global__ __launch_bounds__(256) void k_sort_prep(Ws ws, const uint32_t *depth_
 // strides over the keys, so each global bin receives few atomics.
 constexpr int kHistCopies = 8;
 
-template <class S>
-__global__ __launch_bounds__(S::kThreads) void k_sort_hist(Ws ws, int passes) {
+// FOLD (items of frames of at most kFoldParts preprocess workgroups): no
+// k_sort_prep launch came before.  Every workgroup folds all depth partials
+// itself, the first one resets the frame header and writes the range, and
+// each clears its partition's look-back words of the first pass.
+template <class S, bool FOLD = false>
+__global__ __launch_bounds__(S::kThreads) void k_sort_hist(Ws ws, int passes, const uint32_t *depth_part,
+                                                           int64_t nparts) {
     using Key = typename S::Key;
     constexpr int kSortThreads = S::kThreads, kSortItems = S::kItems;
     constexpr int kSortBlock = kSortThreads * kSortItems;
-    const Ctl c = S::ctl(ws);
+    Ctl c;
+    if constexpr (FOLD) {
+        static_assert(S::kSegmented, "the item sort");
+        __shared__ uint32_t red[2][kSortThreads / kWave];
+        uint32_t dmin = 0xffffffffu, dmax = 0u;
+        for (int64_t k = threadIdx.x; k < nparts; k += kSortThreads) {
+            dmin = min(dmin, depth_part[2 * k]);
+            dmax = max(dmax, depth_part[2 * k + 1]);
+        }
+        for (int off = kWave / 2; off > 0; off >>= 1) {
+            dmin = min(dmin, (uint32_t)__shfl_xor((int)dmin, off, kWave));
+            dmax = max(dmax, (uint32_t)__shfl_xor((int)dmax, off, kWave));
+        }
+        if (lane_id() == 0) {
+            red[0][threadIdx.x / kWave] = dmin;
+            red[1][threadIdx.x / kWave] = dmax;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kSortThreads / kWave; ++k) {
+            dmin = min(dmin, red[0][k]);
+            dmax = max(dmax, red[1][k]);
+        }
+        c.n = ws.n_items;
+        c.dmin = dmin;
+        c.dmax = dmax;
+        c.dbits = dmax > dmin ? 32 - __clz((int)(dmax - dmin)) : 0;
+        c.total_bits = c.dbits;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            frame_header_reset(ws.hdr);
+            ws.hdr->depth_min = dmin;
+            ws.hdr->depth_max = dmax;
+        }
+        if (threadIdx.x < kRadix) ws.lookback[0][(int64_t)blockIdx.x * kRadix + threadIdx.x] = 0;
+    } else {
+        c = S::ctl(ws);
+    }
     __shared__ uint32_t hist[kMaxPasses][kRadix][kHistCopies];
     const int copy = lane_id() & (kHistCopies - 1);
     for (int i = threadIdx.x; i < kMaxPasses * kRadix * kHistCopies; i += kSortThreads)
@@ -339,7 +394,7 @@ __global__ __launch_bounds__(S::kThreads) void k_onesweep(Ws ws, int pass, int p
     __shared__ uint64_t stab[S::kTabRank ? kSortThreads / kWave : 1][S::kTabRank ? kRadix : 1];
     __shared__ uint32_t bstart[kRadix];
     __shared__ uint32_t goff[kRadix];
-    __shared__ uint32_t scan_lds[kSortThreads / kWave + 1];
+    __shared__ alignas(16) uint32_t scan_lds[2 * kScanLds];
     __shared__ int s_part;
 
     // The look-back words of the next pass are cleared here (this pass does
@@ -347,7 +402,7 @@ __global__ __launch_bounds__(S::kThreads) void k_onesweep(Ws ws, int pass, int p
     {
         uint64_t *next = ws.lookback[(pass + 1) & 1];
         const int64_t slot = blockIdx.x;
-        if (slot < parts && threadIdx.x < kRadix) next[slot * kRadix + threadIdx.x] = 0;
+        if (pass + 1 < passes && slot < parts && threadIdx.x < kRadix) next[slot * kRadix + threadIdx.x] = 0;
     }
 
     // Which passes move data: those inside the key's bits, and (items) whose
@@ -375,7 +430,10 @@ __global__ __launch_bounds__(S::kThreads) void k_onesweep(Ws ws, int pass, int p
     if (pass == passes - 1 && blockIdx.x == 0 && threadIdx.x == 0) S::done(ws, nrun_total);
     if (!run_this) return;
 
-    if (threadIdx.x == 0) s_part = (int)atomicAdd(&ws.pctr[pass * kGhStride], 1u);
+    // (a segmented sort's workgroup takes the next partition of its view)
+    const int64_t own_seg = S::kSegmented && PP.ppv > 0 ? (int64_t)blockIdx.x / PP.ppv : 0;
+    if (threadIdx.x == 0)
+        s_part = (int)(own_seg * PP.ppv + atomicAdd(part_counter<S>(ws, own_seg, pass), 1u));
     for (int i = threadIdx.x; i < (kSortThreads / kWave) * kRadix; i += kSortThreads)
         (&whist[0][0])[i] = 0;
     if constexpr (S::kTabRank)
@@ -409,6 +467,10 @@ __global__ __launch_bounds__(S::kThreads) void k_onesweep(Ws ws, int pass, int p
         key[r] = kin[jc];
         if constexpr (S::kHasVal) val[r] = vin[jc];
     }
+    // the segment's total of this thread's digit, in flight with the keys
+    const int d = threadIdx.x;
+    const bool dig = d < kRadix;
+    const uint32_t dtotal = dig ? *digit_bin<S>(ws, segment, pass, d) : 0u;
 #pragma unroll
     for (int r = 0; r < kSortItems; ++r) {
         const int64_t j = wbase + (int64_t)r * kWave + lane;
@@ -439,8 +501,6 @@ __global__ __launch_bounds__(S::kThreads) void k_onesweep(Ws ws, int pass, int p
     // exclusive per-wave offsets and publish the partition's count of the
     // digit at once; the keys are then staged digit-sorted in LDS (their
     // registers free) before the look-back for the global offsets.
-    const int d = threadIdx.x;
-    const bool dig = d < kRadix;
     uint32_t acc = 0;
     uint64_t *lb = ws.lookback[pass & 1];
     if (dig) {
@@ -455,9 +515,9 @@ __global__ __launch_bounds__(S::kThreads) void k_onesweep(Ws ws, int pass, int p
     }
     // global start of digit d (keys with smaller digits) and its start in
     // this partition
-    uint32_t tot;
-    const uint32_t dstart = block_excl_scan(dig ? *digit_bin<S>(ws, segment, pass, d) : 0u, scan_lds, &tot);
-    const uint32_t bs = block_excl_scan(acc, scan_lds, &tot);
+    uint32_t sc[2] = {dtotal, acc}, tot[2];
+    block_excl_scans<2>(sc, scan_lds, tot);
+    const uint32_t dstart = sc[0], bs = sc[1];
     if (dig) bstart[d] = bs;
     __syncthreads();
 #pragma unroll
@@ -560,7 +620,7 @@ __global__ __launch_bounds__(kViewSortThreads) void k_sort_view(Ws ws, const xg_
     uint32_t *whist = lds + N + N / 2;                                    // [NW][kRadix]
     uint64_t *stab = reinterpret_cast<uint64_t *>(whist + NW * kRadix);   // [NW][kRadix]
     __shared__ uint32_t dstart[kRadix];
-    __shared__ uint32_t scan_lds[NW + 1];
+    __shared__ alignas(16) uint32_t scan_lds[kScanLds];
     __shared__ uint32_t red[2][NW];
     const int tid = threadIdx.x, w = tid / kWave, lane = lane_id();
     const int v = blockIdx.x, n = ws.n;
@@ -810,7 +870,7 @@ __global__ __launch_bounds__(256) void k_ranges(Ws ws) {
 
 __global__ __launch_bounds__(1024) void k_tile_order(Ws ws) {
     __shared__ uint32_t hist[kOrderBuckets];
-    __shared__ uint32_t scan_lds[1024 / kWave + 1];
+    __shared__ alignas(16) uint32_t scan_lds[kScanLds];
     const int64_t nt = ws.total_tiles;
     for (int b = threadIdx.x; b < kOrderBuckets; b += blockDim.x) hist[b] = 0;
     __syncthreads();
@@ -832,7 +892,7 @@ __global__ __launch_bounds__(1024) void k_tile_order(Ws ws) {
 // XCD), for the list paths whose last kernel does not write it.
 __global__ __launch_bounds__(1024) void k_xcd_order(Ws ws) {
     __shared__ uint32_t hist[kOrderBuckets];
-    __shared__ uint32_t scan_lds[1024 / kWave + 1];
+    __shared__ alignas(16) uint32_t scan_lds[kScanLds];
     __shared__ uint32_t group[kOrderGroups];
     xcd_order_block(ws, blockIdx.x, hist, scan_lds, group);
 }
@@ -865,12 +925,17 @@ template <class S>
 hipError_t radix_passes(const Ws &ws, int passes, int blocks, hipStream_t s,
                         const uint32_t *depth_part = nullptr, int64_t nparts = 0) {
     const unsigned nb = (unsigned)(blocks > 0 ? blocks : 1);
-    unsigned np = (unsigned)(((int64_t)blocks * kRadix + 255) / 256);
-    if (np > 2048) np = 2048;
-    hipLaunchKernelGGL(k_sort_prep<S>, dim3(np > 0 ? np : 1), dim3(256), 0, s, ws, depth_part, nparts);
-    // segmented sorts: one histogram workgroup per partition
-    const unsigned nh = S::kSegmented ? nb : (nb < 256 ? nb : 256);
-    hipLaunchKernelGGL(k_sort_hist<S>, dim3(nh), dim3(S::kThreads), 0, s, ws, passes);
+    if (S::kSegmented && ws.sort_fold) {
+        hipLaunchKernelGGL((k_sort_hist<ItemSort, true>), dim3(nb), dim3(ItemSort::kThreads), 0, s, ws, passes,
+                           depth_part, nparts);
+    } else {
+        unsigned np = (unsigned)(((int64_t)blocks * kRadix + 255) / 256);
+        if (np > 2048) np = 2048;
+        hipLaunchKernelGGL(k_sort_prep<S>, dim3(np > 0 ? np : 1), dim3(256), 0, s, ws, depth_part, nparts);
+        // segmented sorts: one histogram workgroup per partition
+        const unsigned nh = S::kSegmented ? nb : (nb < 256 ? nb : 256);
+        hipLaunchKernelGGL((k_sort_hist<S, false>), dim3(nh), dim3(S::kThreads), 0, s, ws, passes, nullptr, (int64_t)0);
+    }
     for (int p = 0; p < passes; ++p)
         hipLaunchKernelGGL(k_onesweep<S>, dim3(nb), dim3(S::kThreads), 0, s, ws, p, passes);
     return hipGetLastError();
