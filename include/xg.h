@@ -191,8 +191,8 @@ xg_status xg_preprocess(const xg_frame *f /* [host] */, const xg_gaussians *g /*
  * depth.  The (view, Gaussian) items of each view are radix-sorted stably
  * by depth on the depth bits that vary, and their tile counts are scanned
  * in that order (offsets).  One (global tile id, Gaussian index) pair per
- * (view, Gaussian, tile) is then placed in tile order: when every view has
- * at most 4096 tiles, directly at its list position by a stable counting
+ * (view, Gaussian, tile) is then placed in tile order: unless the views
+ * have very many tiles, directly at its list position by a stable counting
  * sort of each view's pairs by tile; otherwise emitted in item order and
  * radix-sorted stably by tile id.  A tile lists only Gaussians of its own
  * view, so either way the result equals a sort of the keys (tile << 32 |

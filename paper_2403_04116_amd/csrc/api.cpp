@@ -72,10 +72,10 @@ xg_status check_frame(const xg_frame *f, bool need_ws, int64_t *tot_px, int64_t 
 
 struct Plan {
     xg_ws_layout lay;
-    size_t icounts, scan_tmp, ikeys[2], ivals[2], ptile[2], pval[2], ghist, vhist, vctr, bin_cnt, bin_ptot,
+    size_t icounts, scan_tmp, ikeys[2], ivals[2], ptile[2], pval[2], ghist, vhist, vctr, bin_cnt, bin_csum, bin_ptot,
         bin_pstart, lookback[2], tile_order, xcd_order, blend_order, ssim, entry_mask;
     int64_t total_px, total_tiles, n_items;
-    int32_t item_blocks, pair_blocks, tile_bits, pair_passes, pair_gbits, bin_tiles, bin_ppv, bin_items;
+    int32_t item_blocks, pair_blocks, tile_bits, pair_passes, pair_gbits, bin_tiles, bin_bands, bin_ppv, bin_items;
     ViewSort view_sort;
     bool sort_fold;
 };
@@ -90,13 +90,27 @@ xg_status make_plan(const xg_frame *f, bool need_ws, Plan &P) {
     P.n_items = ni;
     // the items are sorted within each view: every view starts a partition
     P.item_blocks = (int32_t)((int64_t)f->n_views * (((int64_t)f->n + kItemSortBlock - 1) / kItemSortBlock));
-    // tile lists by counting when every view has at most kBinMaxTiles tiles
-    int64_t max_view_tiles = 0;
+    // Tile lists by counting, in rows of at most kBinMaxTilesX tiles, when
+    // every view has at most 4096 tiles, or more but not many ranking
+    // workgroups (partitions x bands): each of those reads its partition
+    // anew, and the radix sort of the pairs does not.  Counting against
+    // emission and radix sort, whole forward pass: 200k Gaussians, one view of
+    // 2048 x 1536 (1176 workgroups) 237 us against 293; 500k, 2048 x 2048
+    // (3920) 335 against 360; 1M, 2048 x 2048 (7824) 497 against 459.
+    int64_t max_view_tiles = 0, max_tiles_x = 0;
+    P.bin_bands = 1;
     for (int v = 0; v < f->n_views; ++v) {
         const int64_t t = tiles_of(f->cams[v], f->settings.tile);
-        if (t > max_view_tiles) max_view_tiles = t;
+        const int64_t tx = (f->cams[v].width + f->settings.tile - 1) / f->settings.tile;
+        max_view_tiles = std::max(max_view_tiles, t);
+        max_tiles_x = std::max(max_tiles_x, tx);
+        if (tx > kBinMaxTilesX) continue;
+        const int64_t rows = kBinMaxTilesX / tx;   // tile rows of a band
+        P.bin_bands = (int32_t)std::max<int64_t>(P.bin_bands, (t / tx + rows - 1) / rows);
     }
-    P.bin_tiles = max_view_tiles <= kBinMaxTiles ? (int32_t)max_view_tiles : 0;
+    const int64_t groups = f->n_views * (((int64_t)f->n + kBinItems - 1) / kBinItems) * P.bin_bands;
+    const bool few = max_view_tiles <= kBinMaxTiles || (max_view_tiles <= kBinMostTiles && groups <= kBinMostGroups);
+    P.bin_tiles = few && max_tiles_x <= kBinMaxTilesX ? (int32_t)max_view_tiles : 0;
     // Partitions as small as still leave every one its own resident ranking
     // workgroup: a frame of few items is otherwise ranked by a handful of
     // workgroups, window after window.  Partitions of 2048 -> by this rule,
@@ -106,7 +120,7 @@ xg_status make_plan(const xg_frame *f, bool need_ws, Plan &P) {
     // 1024 items at 16 M items cost 80 us more than 2048.
     P.bin_items = kBinItems;
     while (P.bin_items > kBinItemsMin &&
-           f->n_views * (((int64_t)f->n + P.bin_items / 2 - 1) / (P.bin_items / 2)) <= kBinResident)
+           f->n_views * (((int64_t)f->n + P.bin_items / 2 - 1) / (P.bin_items / 2)) * P.bin_bands <= kBinResident)
         P.bin_items /= 2;
     // A view of at most 8192 items is sorted by one workgroup in LDS instead
     // of the radix passes' six launches (8000 items, one view: 20 us less; 400
@@ -167,6 +181,7 @@ xg_status make_plan(const xg_frame *f, bool need_ws, Plan &P) {
     P.vhist = o;              o = align_up(o + 4 * (size_t)f->n_views * kMaxPasses * kRadix);
     P.vctr = o;               o = align_up(o + 4 * (size_t)f->n_views * kMaxPasses * kGhStride);
     P.bin_cnt = o;            o = align_up(o + 4 * (size_t)f->n_views * P.bin_ppv * P.bin_tiles);
+    P.bin_csum = o;           o = align_up(o + 4 * (size_t)f->n_views * ((P.bin_tiles + kColTiles - 1) / kColTiles));
     P.bin_ptot = o;           o = align_up(o + 4 * (size_t)f->n_views * P.bin_ppv);
     P.bin_pstart = o;         o = align_up(o + 4 * (size_t)f->n_views * P.bin_ppv);
     for (int b = 0; b < 2; ++b) { P.lookback[b] = o; o = align_up(o + 8 * (size_t)lb_words); }
@@ -205,9 +220,11 @@ Ws resolve(const xg_frame *f, const Plan &P) {
     w.vctr = (uint32_t *)(b + P.vctr);
     w.sort_fold = P.sort_fold;
     w.bin_cnt = (uint32_t *)(b + P.bin_cnt);
+    w.bin_csum = (uint32_t *)(b + P.bin_csum);
     w.bin_ptot = (uint32_t *)(b + P.bin_ptot);
     w.bin_pstart = (uint32_t *)(b + P.bin_pstart);
     w.bin_tiles = P.bin_tiles;
+    w.bin_bands = P.bin_bands;
     w.bin_ppv = P.bin_ppv;
     w.bin_items = P.bin_items;
     w.view_sort = P.view_sort;

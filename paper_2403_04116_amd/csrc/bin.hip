@@ -6,16 +6,18 @@
 // order, and their scanned tile counts give every item its pair slots.  A
 // tile only lists Gaussians of its own view, in item order.  The lists are
 // therefore a stable counting sort of each view's pairs by view-local tile
-// id, whose digit range (the view's tiles, at most kBinMaxTiles) is small
-// enough to count in LDS:
+// id, whose digit range (the view's tiles, bounded by the plan) is small
+// enough to count in LDS, in bands of whole tile rows where a view has more
+// tiles than one workgroup's counters (each band a workgroup of its own, its
+// items' rectangles clipped to it):
 //   1. k_bin_count: per partition (ws.bin_items consecutive items of one
 //      view), the number of pairs of each tile (LDS atomics over the items'
 //      tile rectangles) -> one row of bin_cnt;
 //   2. k_bin_columns: down each (view, tile) column of bin_cnt, the
 //      exclusive scan over the view's partitions (segments in parallel),
 //      and the tile's total;
-//   3. k_bin_starts: per view, the exclusive scan of the tile totals from
-//      the view's first pair slot -> the tile ranges [start, end);
+//   3. k_bin_starts: the exclusive scan of a view's tile totals from the
+//      view's first pair slot -> the tile ranges [start, end);
 //   4. k_bin_scatter: per partition, the pairs in windows of kBinWindow
 //      slots: emitted into LDS in slot order, ranked stably within the
 //      window (each row of 64 slots matched by tile through an LDS table of
@@ -34,7 +36,21 @@ namespace {
 struct BinPart {
     int view, q;
     int64_t j0, j1;   // items [j0, j1) of the partition
-    int tiles_x, tiles, toff;
+    int tiles_x, tiles_y, tiles, toff;
+};
+
+// Rows [y0, y1] of tiles of band `band`, and its first tile and tile count;
+// bands hold at most `most` tiles, and tiles_x is at most that.  A band past
+// the view's last row is empty.
+struct Band {
+    int y0, y1, first, tiles;
+    __device__ __forceinline__ Band(const BinPart &b, int band, int most) {
+        const int rows = most / b.tiles_x;
+        y0 = min(band * rows, b.tiles_y);
+        y1 = min(y0 + rows, b.tiles_y) - 1;
+        first = y0 * b.tiles_x;
+        tiles = (y1 - y0 + 1) * b.tiles_x;
+    }
 };
 
 __device__ __forceinline__ BinPart bin_part(const Ws &ws, const xg_camera *cams, int tile, int part) {
@@ -46,23 +62,29 @@ __device__ __forceinline__ BinPart bin_part(const Ws &ws, const xg_camera *cams,
     b.j1 = min(b.j0 + ws.bin_items, vbase + ws.n);
     const xg_camera &c = cams[b.view];
     b.tiles_x = (c.width + tile - 1) / tile;
-    b.tiles = b.tiles_x * ((c.height + tile - 1) / tile);
+    b.tiles_y = (c.height + tile - 1) / tile;
+    b.tiles = b.tiles_x * b.tiles_y;
     b.toff = c.tile_offset;
     return b;
 }
 
-constexpr int kCountThreads = 256;
+constexpr int kCountThreads = 1024;
+constexpr int kCountTiles = 4096;     // tiles of a band of the counting kernel
+constexpr int kScatterTiles = 1024;   // and of the ranking kernel
+static_assert(kBinMaxTilesX <= kScatterTiles && kBinMaxTilesX <= kCountTiles, "a band holds a row of tiles");
 static_assert(kBinItems % kCountThreads == 0, "whole items per thread");
 
-__global__ __launch_bounds__(kCountThreads) void k_bin_count(Ws ws, const xg_camera *cams, int tile) {
-    __shared__ uint32_t cnt[kBinMaxTiles];
-    const BinPart b = bin_part(ws, cams, tile, blockIdx.x);
+__global__ __launch_bounds__(kCountThreads) void k_bin_count(Ws ws, const xg_camera *cams, int tile, int bands) {
+    __shared__ uint32_t cnt[kCountTiles];
+    const int part = (int)blockIdx.x / bands;
+    const BinPart b = bin_part(ws, cams, tile, part);
+    const Band bd(b, (int)blockIdx.x - part * bands, kCountTiles);
     // the item sort is over: leave its digit totals and counters zero
     if (ws.sort_fold)
         for (int64_t i = (int64_t)blockIdx.x * kCountThreads + threadIdx.x; i < item_sort_zeros(ws);
              i += (int64_t)gridDim.x * kCountThreads)
             zero_item_sort(ws, i);
-    for (int t = threadIdx.x; t < b.tiles; t += kCountThreads) cnt[t] = 0;
+    for (int t = threadIdx.x; t < bd.tiles; t += kCountThreads) cnt[t] = 0;
     __syncthreads();
     const int sel = ws.hdr->item_sel & 1;
     // every item's count and sort value loaded before any is used
@@ -81,10 +103,11 @@ __global__ __launch_bounds__(kCountThreads) void k_bin_count(Ws ws, const xg_cam
         if (n_t[k] == 0) continue;
         mine += n_t[k];
         const TileRect r = item_tile_rect(ws, val[k], tile);
-        for (int ty = r.ty0; ty <= r.ty1; ++ty)
-            for (int tx = r.tx0; tx <= r.tx1; ++tx) atomicAdd(&cnt[ty * b.tiles_x + tx], 1u);
+        for (int ty = max(r.ty0, bd.y0); ty <= min(r.ty1, bd.y1); ++ty)
+            for (int tx = r.tx0; tx <= r.tx1; ++tx) atomicAdd(&cnt[ty * b.tiles_x + tx - bd.first], 1u);
     }
-    // the partition's pair total (at most kBinItems * kBinMaxTiles)
+    // the partition's pair total, by its first band's workgroup (at most
+    // kBinItems * kBinMostTiles)
     __shared__ uint32_t s_tot[kCountThreads / kWave];
     for (int off = kWave / 2; off > 0; off >>= 1) mine += (uint32_t)__shfl_xor((int)mine, off, kWave);
     if (lane_id() == 0) s_tot[threadIdx.x / kWave] = mine;
@@ -93,19 +116,19 @@ __global__ __launch_bounds__(kCountThreads) void k_bin_count(Ws ws, const xg_cam
         uint32_t tot = 0;
 #pragma unroll
         for (int w = 0; w < kCountThreads / kWave; ++w) tot += s_tot[w];
-        ws.bin_ptot[blockIdx.x] = tot;
+        if (bd.y0 == 0) ws.bin_ptot[part] = tot;
     }
-    uint32_t *row = ws.bin_cnt + (int64_t)blockIdx.x * ws.bin_tiles;
-    for (int t = threadIdx.x; t < b.tiles; t += kCountThreads) row[t] = cnt[t];
+    uint32_t *row = ws.bin_cnt + (int64_t)part * ws.bin_tiles + bd.first;
+    for (int t = threadIdx.x; t < bd.tiles; t += kCountThreads) row[t] = cnt[t];
 }
 
 // Exclusive scan down each (view, local tile) column of bin_cnt over the
 // view's partitions, rewritten in place; the column total goes to the
-// tile's range start word until k_bin_starts replaces it.  A workgroup
-// takes 64 columns; its wavefronts split each column's partitions into
+// tile's range start word until k_bin_starts replaces it, and the sum of the
+// workgroup's columns to bin_csum.  A workgroup takes 64 columns; its wavefronts split each column's partitions into
 // kColSegs consecutive segments: each sums its segment, the segment totals are
 // scanned through LDS, and each rewrites its segment from its offset.
-constexpr int kColTiles = 64;
+static_assert(kColTiles == kWave, "a wavefront adds up a workgroup's columns");
 constexpr int kColSegs = 8;
 constexpr int kColThreads = kColTiles * kColSegs;
 
@@ -136,7 +159,6 @@ __global__ __launch_bounds__(kColThreads) void k_bin_columns(Ws ws, const xg_cam
     }
     part[seg][threadIdx.x % kColTiles] = sum;
     __syncthreads();
-    if (!live) return;
     uint32_t run = 0, total = 0;
 #pragma unroll
     for (int k = 0; k < kColSegs; ++k) {
@@ -144,6 +166,12 @@ __global__ __launch_bounds__(kColThreads) void k_bin_columns(Ws ws, const xg_cam
         run += k < seg ? x : 0u;
         total += x;
     }
+    if (seg == 0) {   // one wavefront: the pairs of the workgroup's tiles
+        uint32_t sum = total;
+        for (int off = kWave / 2; off > 0; off >>= 1) sum += (uint32_t)__shfl_xor((int)sum, off, kWave);
+        if (lane_id() == 0) ws.bin_csum[blockIdx.x] = sum;
+    }
+    if (!live) return;
     int q = q0;
     for (; q + 8 <= q1; q += 8) {
         uint32_t x[8];
@@ -163,48 +191,64 @@ __global__ __launch_bounds__(kColThreads) void k_bin_columns(Ws ws, const xg_cam
     if (seg == kColSegs - 1) ws.ranges[2 * ((int64_t)c.tile_offset + t)] = total;
 }
 
-// One workgroup per view.  The view's first pair slot is the sum of the
-// pair totals of the partitions of the views before it; the pair count of
-// the whole frame (every workgroup sums all partitions) is checked against
-// the capacity (XG_ECAPACITY, and the pair count, written by the first
-// workgroup).  Then the exclusive scan of the view's partition totals
-// gives each partition's first slot, and the scan of the tile totals the
-// tile ranges.  Empty tiles, and all tiles once the capacity is exceeded,
-// read (0, 0).
+// One workgroup per kStartThreads tiles of a view.  The view's first pair
+// slot is the sum of the pair totals of the partitions of the views before
+// it; the pair count of the whole frame (every workgroup sums all
+// partitions) is checked against the capacity (XG_ECAPACITY, and the pair
+// count, written by the first workgroup).  The view's first workgroup scans
+// its partition totals into each partition's first slot.  The tile ranges
+// are the scan of the tile totals, from the sums of the column workgroups
+// before.  Empty tiles, and all tiles once the capacity is exceeded, read
+// (0, 0).  (One workgroup for a whole view reads a large view's totals at
+// the rate of one CU's outstanding loads: 15 us for 12 288 tiles.)
 constexpr int kStartThreads = 1024;
 
-__global__ __launch_bounds__(kStartThreads) void k_bin_starts(Ws ws, const xg_camera *cams, int tile) {
+__global__ __launch_bounds__(kStartThreads) void k_bin_starts(Ws ws, const xg_camera *cams, int tile, int blocks,
+                                                              int chunks) {
     __shared__ alignas(16) uint32_t lds[kScanLds];
-    __shared__ uint64_t s_sum[2][kStartThreads / kWave];
-    const int v = blockIdx.x;
+    __shared__ uint64_t s_sum[3][kStartThreads / kWave];
+    const int v = (int)blockIdx.x / blocks, blk = (int)blockIdx.x - v * blocks;
     const xg_camera &c = cams[v];
     const int tiles = ((c.width + tile - 1) / tile) * ((c.height + tile - 1) / tile);
+    uint2 *rg = reinterpret_cast<uint2 *>(ws.ranges) + c.tile_offset;
+    const int t = blk * kStartThreads + (int)threadIdx.x;
+    const uint32_t n = t < tiles ? rg[t].x : 0u;
     const int ppv = ws.bin_ppv;
     const int64_t nparts = (int64_t)ws.n_views * ppv;
-    uint64_t before = 0, all = 0;
+    uint64_t before = 0, all = 0, columns = 0;
     for (int64_t k = threadIdx.x; k < nparts; k += kStartThreads) {
         const uint32_t x = ws.bin_ptot[k];
         all += x;
         if (k < (int64_t)v * ppv) before += x;
     }
+    for (int k = threadIdx.x; k < min(blk * (kStartThreads / kColTiles), chunks); k += kStartThreads)
+        columns += ws.bin_csum[(int64_t)v * chunks + k];
     for (int off = kWave / 2; off > 0; off >>= 1) {
         before += __shfl_xor(before, off, kWave);
         all += __shfl_xor(all, off, kWave);
+        columns += __shfl_xor(columns, off, kWave);
     }
     if (lane_id() == 0) {
         s_sum[0][threadIdx.x / kWave] = before;
         s_sum[1][threadIdx.x / kWave] = all;
+        s_sum[2][threadIdx.x / kWave] = columns;
     }
     __syncthreads();
     before = 0;
     all = 0;
+    columns = 0;
 #pragma unroll
     for (int w = 0; w < kStartThreads / kWave; ++w) {
         before += s_sum[0][w];
         all += s_sum[1][w];
+        columns += s_sum[2][w];
     }
     const bool st_ok = ws.hdr->status == XG_OK;   // an item sort that gave up keeps its XG_EHIP
     const bool ok = st_ok && all <= (uint64_t)ws.cap;
+    uint32_t tot;
+    const uint32_t start = (uint32_t)(before + columns) + block_excl_scan(n, lds, &tot);
+    if (t < tiles) rg[t] = ok && n > 0 ? make_uint2(start, start + n) : make_uint2(0u, 0u);
+    if (blk > 0) return;
     if (v == 0 && threadIdx.x == 0) {
         ws.hdr->n_pairs = (int32_t)(all > 0x7fffffffull ? 0x7fffffffull : all);
         if (st_ok && all > (uint64_t)ws.cap) ws.hdr->status = XG_ECAPACITY;
@@ -214,29 +258,15 @@ __global__ __launch_bounds__(kStartThreads) void k_bin_starts(Ws ws, const xg_ca
     for (int q0 = 0; q0 < ppv; q0 += kStartThreads) {
         const int q = q0 + threadIdx.x;
         const uint32_t x = q < ppv ? ws.bin_ptot[(int64_t)v * ppv + q] : 0u;
-        uint32_t tot;
         const uint32_t ex = block_excl_scan(x, lds, &tot);
         if (q < ppv) ws.bin_pstart[(int64_t)v * ppv + q] = carry + ex;
         carry += tot;
     }
-    carry = (uint32_t)before;
-    uint32_t *rg = ws.ranges + 2 * (int64_t)c.tile_offset;
-    for (int t0 = 0; t0 < tiles; t0 += kStartThreads) {
-        const int t = t0 + threadIdx.x;
-        const uint32_t n = t < tiles ? rg[2 * t] : 0u;
-        uint32_t tot;
-        const uint32_t ex = block_excl_scan(n, lds, &tot);
-        if (t < tiles) {
-            const bool live = ok && n > 0;
-            rg[2 * t] = live ? carry + ex : 0u;
-            rg[2 * t + 1] = live ? carry + ex + n : 0u;
-        }
-        carry += tot;
-    }
 }
 
-// Stable ranking and placement of one partition's pairs.  NW wavefronts;
-// LT = the most view-local tiles supported (LB bits).  Per window: the
+// Stable ranking and placement of one partition's pairs in one band of its
+// view's tile rows (LT tiles at most; most views have a single band).  The
+// pairs of the band are numbered in item order (slots).  Per window: the
 // pairs of slots [w0, w0 + kBinWindow) are emitted into LDS in slot order;
 // wavefront w ranks its kBinWindow / NW consecutive slots, row by row (the
 // lanes of a row holding a tile found through the lane-mask table), with a
@@ -248,13 +278,16 @@ __global__ __launch_bounds__(kStartThreads) void k_bin_starts(Ws ws, const xg_ca
 // pairs are first permuted in LDS into blocks of one tile each (a
 // wavefront scan of the tile totals), so that the stores of a row write
 // runs of consecutive list entries.
-// (16 wavefronts: at most 64 registers, so that two workgroups share a CU)
+// (16 wavefronts, at most 64 registers, so that two workgroups share a CU.
+// Bands of 4096 tiles, whose counters leave 8 wavefronts on a CU: 200k
+// Gaussians, 8 views of 4096 tiles, 0.64 ms a forward pass where bands of 1024
+// take 0.52.)
 // MI = items per thread: the partitions hold at most MI NT items.
-template <int LT, int NW, int MI>
-__global__ __launch_bounds__(NW * kWave, NW == 16 ? 8 : 2) void k_bin_scatter(Ws ws, const xg_camera *cams,
-                                                                              int tile) {
+template <int MI>
+__global__ __launch_bounds__(1024, 8) void k_bin_scatter(Ws ws, const xg_camera *cams, int tile, int bands) {
+    constexpr int LT = kScatterTiles, NW = 16;
     constexpr int NT = NW * kWave;
-    constexpr int LB = LT <= 1024 ? 10 : 12;
+    constexpr int LB = 10;
     constexpr int kRows = kBinWindow / NT;         // rows of 64 slots per wavefront
     constexpr int kMyItems = MI;
     static_assert(LT <= (1 << LB) && kBinWindow % NT == 0, "shape");
@@ -281,27 +314,24 @@ __global__ __launch_bounds__(NW * kWave, NW == 16 ? 8 : 2) void k_bin_scatter(Ws
         xcd_order_block(ws, blockIdx.x, base, s_lst, &h16[0][0]);
         return;
     }
-    const int part = (int)blockIdx.x - kXcds;
+    const int part = ((int)blockIdx.x - kXcds) / bands;
     if (ws.hdr->status != XG_OK) return;
     const BinPart b = bin_part(ws, cams, tile, part);
-    if (b.j0 >= b.j1) return;
-    // the partition's pair slots [S, E)
-    const uint32_t S = ws.bin_pstart[part];
-    const uint32_t E = S + ws.bin_ptot[part];
+    const Band bd(b, (int)blockIdx.x - kXcds - part * bands, LT);
+    if (b.j0 >= b.j1 || bd.tiles <= 0) return;
 
     for (int k = threadIdx.x; k < NW * kHash; k += NT) (&s_tab[0][0])[k] = 0ull;
-    const uint32_t *colp = ws.bin_cnt + (int64_t)part * ws.bin_tiles;
-    for (int t = threadIdx.x; t < b.tiles; t += NT)
-        base[t] = ws.ranges[2 * ((int64_t)b.toff + t)] + colp[t];
+    const uint32_t *colp = ws.bin_cnt + (int64_t)part * ws.bin_tiles + bd.first;
+    for (int t = threadIdx.x; t < bd.tiles; t += NT)
+        base[t] = ws.ranges[2 * ((int64_t)b.toff + bd.first + t)] + colp[t];
 
-    // this thread's items: slot range (the exclusive scan of the item
-    // counts in item order, from S; also written to offsets), view-local
-    // tile rectangle, index
+    // this thread's items: slot range (the exclusive scan of the items'
+    // pairs in the band, in item order), tile rectangle clipped to the band,
+    // index
     const int sel = ws.hdr->item_sel & 1;
-    // (a view has at most kBinMaxTiles tiles: counts and tile coordinates
-    // fit 16 bits)
+    // (counts and tile coordinates in the band fit 16 bits)
     uint32_t i_off[kMyItems], i_gi[kMyItems];
-    uint32_t i_cy[kMyItems];  // pair count | first tile row << 16
+    uint32_t i_cy[kMyItems];  // pair count | first tile row of the band << 16
     uint32_t i_x[kMyItems];   // first | last tile column << 16
 #pragma unroll
     for (int k = 0; k < kMyItems; ++k) {
@@ -316,36 +346,40 @@ __global__ __launch_bounds__(NW * kWave, NW == 16 ? 8 : 2) void k_bin_scatter(Ws
                 const uint64_t val = ws.ivals[sel][j];
                 i_gi[k] = (uint32_t)val - (uint32_t)b.view * (uint32_t)ws.n;
                 const TileRect r = item_tile_rect(ws, val, tile);
+                const int y0 = max(r.ty0, bd.y0), y1 = min(r.ty1, bd.y1);
                 i_x[k] = (uint32_t)r.tx0 | ((uint32_t)r.tx1 << 16);
-                i_cy[k] = cnt | ((uint32_t)r.ty0 << 16);
+                if (y0 <= y1)
+                    i_cy[k] = (uint32_t)((r.tx1 - r.tx0 + 1) * (y1 - y0 + 1)) | ((uint32_t)(y0 - bd.y0) << 16);
             }
         }
     }
+    // a thread's items are consecutive (j0 + thread kMyItems + k): one block
+    // scan of the thread sums, of the band's pairs and, for the first band's
+    // workgroup, of the items' whole counts (the offsets, from the
+    // partition's first pair)
+    uint32_t E;
     {
-        // a thread's items are consecutive (j0 + thread kMyItems + k): one
-        // wavefront scan of the thread sums, the wavefront totals through LDS
-        __shared__ uint4 s_wt[NW / 4];
-        static_assert(NW % 4 == 0, "wavefront totals read four at a time");
-        const int wv = threadIdx.x / kWave;
-        uint32_t mine = 0;
+        __shared__ alignas(16) uint32_t s_scan[2 * kScanLds];
+        uint32_t sums[2] = {0, 0}, tot[2];
 #pragma unroll
-        for (int k = 0; k < kMyItems; ++k) mine += i_cy[k] & 0xffffu;
-        const uint32_t inc = wave_incl_scan(mine);
-        if (lane_id() == kWave - 1) reinterpret_cast<uint32_t *>(s_wt)[wv] = inc;
-        __syncthreads();
-        uint32_t run = S + inc - mine;
+        for (int k = 0; k < kMyItems; ++k) sums[0] += i_cy[k] & 0xffffu;
+        uint32_t whole[kMyItems];
 #pragma unroll
-        for (int x4 = 0; x4 < NW / 4; ++x4) {
-            const uint4 t = s_wt[x4];
-            run += (4 * x4 < wv ? t.x : 0u) + (4 * x4 + 1 < wv ? t.y : 0u) +
-                   (4 * x4 + 2 < wv ? t.z : 0u) + (4 * x4 + 3 < wv ? t.w : 0u);
+        for (int k = 0; k < kMyItems; ++k) {
+            const int64_t j = b.j0 + (int64_t)threadIdx.x * kMyItems + k;
+            whole[k] = bands > 1 && bd.y0 == 0 && j < b.j1 ? ws.icounts[j] : i_cy[k] & 0xffffu;
+            sums[1] += whole[k];
         }
+        block_excl_scans<2>(sums, s_scan, tot);
+        E = tot[0];
+        uint32_t run = sums[0], off = ws.bin_pstart[part] + sums[1];
 #pragma unroll
         for (int k = 0; k < kMyItems; ++k) {
             i_off[k] = run;
             run += i_cy[k] & 0xffffu;
             const int64_t j = b.j0 + (int64_t)threadIdx.x * kMyItems + k;
-            if (j < b.j1) ws.offsets[j] = i_off[k];
+            if (bd.y0 == 0 && j < b.j1) ws.offsets[j] = off;
+            off += whole[k];
         }
     }
 
@@ -356,7 +390,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 16 ? 8 : 2) void k_bin_scatter(Ws
     uint32_t *out_t = ws.ptile[ws.pair_sel];
     uint32_t *out_v = ws.pval[ws.pair_sel];
 
-    for (uint32_t w0 = S; w0 < E; w0 += kBinWindow) {
+    for (uint32_t w0 = 0; w0 < E; w0 += kBinWindow) {
         const uint32_t w1 = min(E, w0 + (uint32_t)kBinWindow);
         const int wn = (int)(w1 - w0);
         for (int k = threadIdx.x; k < NW * (LT / 2); k += NT) (&h16[0][0])[k] = 0u;
@@ -469,7 +503,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 16 ? 8 : 2) void k_bin_scatter(Ws
                 const uint32_t gi = s_gi[slot];
                 const uint32_t st = (s_lst[t >> 1] >> (16u * (t & 1u))) & 0xffffu;
                 const uint32_t dst = base[t] + ((uint32_t)k - st);
-                const uint32_t gt = (uint32_t)b.toff + t;
+                const uint32_t gt = (uint32_t)(b.toff + bd.first) + t;
                 if (dst >= (uint64_t)ws.cap) continue;   // never: the counts add up to the slots
                 if (gb) {
                     out_t[dst] = (gt << gb) | gi;
@@ -484,8 +518,8 @@ __global__ __launch_bounds__(NW * kWave, NW == 16 ? 8 : 2) void k_bin_scatter(Ws
         for (int k = 0; k < kPairsPerThread; ++k) {
             const int tw = k * NT + threadIdx.x;
             if (tw < LT / 2) {
-                if (2 * tw < b.tiles) base[2 * tw] += adv[k] & 0xffffu;
-                if (2 * tw + 1 < b.tiles) base[2 * tw + 1] += adv[k] >> 16;
+                if (2 * tw < bd.tiles) base[2 * tw] += adv[k] & 0xffffu;
+                if (2 * tw + 1 < bd.tiles) base[2 * tw + 1] += adv[k] >> 16;
             }
         }
         // the next window's counters are cleared before its ranking, after
@@ -496,32 +530,29 @@ __global__ __launch_bounds__(NW * kWave, NW == 16 ? 8 : 2) void k_bin_scatter(Ws
 }  // namespace
 
 hipError_t launch_bin_lists(const Ws &ws, const xg_camera *cams, const Params &p, hipStream_t s) {
-    if (ws.bin_tiles <= 0 || ws.bin_tiles > kBinMaxTiles || ws.bin_ppv <= 0 || ws.bin_items <= 0 ||
-        ws.bin_items > kBinItems)
+    if (ws.bin_tiles <= 0 || ws.bin_tiles > kBinMostTiles || ws.bin_bands <= 0 || ws.bin_ppv <= 0 ||
+        ws.bin_items <= 0 || ws.bin_items > kBinItems)
         return hipErrorInvalidValue;
     const int64_t parts = (int64_t)ws.n_views * ws.bin_ppv;
-    if (parts > 0x7fffffff) return hipErrorInvalidValue;
-    const unsigned np = (unsigned)parts;
+    // (a counting band of 4 ranking bands' tiles holds at least 4 of them)
+    const int cbands = (ws.bin_bands + kCountTiles / kScatterTiles - 1) / (kCountTiles / kScatterTiles);
+    if (parts * ws.bin_bands + kXcds > 0x7fffffff) return hipErrorInvalidValue;
     if (ws.view_sort != ViewSort::kLists) {   // else counted by the item sort's launch
-        hipLaunchKernelGGL(k_bin_count, dim3(np), dim3(kCountThreads), 0, s, ws, cams, p.tile);
+        hipLaunchKernelGGL(k_bin_count, dim3((unsigned)(parts * cbands)), dim3(kCountThreads), 0, s, ws, cams, p.tile,
+                           cbands);
         const int chunks = (ws.bin_tiles + kColTiles - 1) / kColTiles;
         hipLaunchKernelGGL(k_bin_columns, dim3((unsigned)(ws.n_views * chunks)), dim3(kColThreads), 0, s, ws,
                            cams, p.tile, chunks);
-        hipLaunchKernelGGL(k_bin_starts, dim3((unsigned)ws.n_views), dim3(kStartThreads), 0, s, ws, cams, p.tile);
+        const int blocks = (ws.bin_tiles + kStartThreads - 1) / kStartThreads;
+        hipLaunchKernelGGL(k_bin_starts, dim3((unsigned)(ws.n_views * blocks)), dim3(kStartThreads), 0, s, ws, cams,
+                           p.tile, blocks, chunks);
     }
     // kXcds extra workgroups write the blend launches' tile order
-    const dim3 grid(np + kXcds);
-    if (ws.bin_tiles <= 1024) {
-        if (ws.bin_items > 1024)
-            hipLaunchKernelGGL((k_bin_scatter<1024, 16, 2>), grid, dim3(16 * kWave), 0, s, ws, cams, p.tile);
-        else
-            hipLaunchKernelGGL((k_bin_scatter<1024, 16, 1>), grid, dim3(16 * kWave), 0, s, ws, cams, p.tile);
-    } else {
-        if (ws.bin_items > 512)
-            hipLaunchKernelGGL((k_bin_scatter<4096, 8, 4>), grid, dim3(8 * kWave), 0, s, ws, cams, p.tile);
-        else
-            hipLaunchKernelGGL((k_bin_scatter<4096, 8, 1>), grid, dim3(8 * kWave), 0, s, ws, cams, p.tile);
-    }
+    const dim3 grid((unsigned)(parts * ws.bin_bands) + kXcds);
+    if (ws.bin_items > 1024)
+        hipLaunchKernelGGL(k_bin_scatter<2>, grid, dim3(1024), 0, s, ws, cams, p.tile, ws.bin_bands);
+    else
+        hipLaunchKernelGGL(k_bin_scatter<1>, grid, dim3(1024), 0, s, ws, cams, p.tile, ws.bin_bands);
     return hipGetLastError();
 }
 

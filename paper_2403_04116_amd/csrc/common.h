@@ -106,6 +106,7 @@ struct Ws {
     bool sort_fold;        // item sort: its histogram launch folds the depth partials (no clearing launch)
     uint32_t *bin_cnt;     // tile lists by counting: [view][partition][local tile] pair counts,
                            // then their exclusive scan down each column
+    uint32_t *bin_csum;    // tile lists by counting: pairs of every 64 tiles of a view
     uint32_t *bin_ptot;    // tile lists by counting: pairs of each [view][partition]
     uint32_t *bin_pstart;  // tile lists by counting: first pair slot of each [view][partition]
     uint32_t *pctr;        // radix sort: partition counters [kMaxPasses]
@@ -141,6 +142,7 @@ struct Ws {
     // most tiles of any view), and per view the partitions of bin_items items.
     // bin_tiles = 0: emission and the radix sort of the pairs by tile.
     int32_t bin_tiles;
+    int32_t bin_bands;     // bands of at most 1024 tiles (whole rows) of the view with the most
     int32_t bin_ppv;
     int32_t bin_items;
     ViewSort view_sort;
@@ -223,6 +225,10 @@ constexpr int kBinItemsMin = 256;
 constexpr int kBinResident = 512;   // ranking workgroups the device holds at once (two per CU)
 constexpr int kBinWindow = 4096;
 constexpr int kBinMaxTiles = 4096;
+constexpr int kBinMaxTilesX = 1024;             // most tiles in a row
+constexpr int kBinMostTiles = 65536;            // most tiles of a view in a frame of few
+constexpr int kBinMostGroups = 4096;            // ranking workgroups
+constexpr int kColTiles = 64;                   // tiles of a workgroup of the column scans
 
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 8;
