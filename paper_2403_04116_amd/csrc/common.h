@@ -32,7 +32,8 @@ static_assert(sizeof(WsHeader) == 256, "header is one 256-byte block");
 // staged list entry is a single aligned gather.
 //   a: (u_x - floor(u_x), u_y - floor(u_y), qa, qb)
 //   b: (qc, -log2(opacity), intensity, float bits of depth)
-//   c: (floor(u_x), floor(u_y), x_lo | x_hi << 16, y_lo | y_hi << 16)
+//   c: (floor(u_x), floor(u_y), x_lo | x_hi << 16, y_lo | y_hi << 16), with
+//      kRecPlain in the x word (bounds are below 2^15)
 //   d: unused
 // (qa, qb, qc) factor the inverse 2-D covariance scaled by k = log2(e)/2:
 //   k * d^T Sigma''^-1 d = (qa dx + qb dy)^2 + (qc dy)^2
@@ -46,6 +47,12 @@ struct alignas(64) Record {
     float4 d;
 };
 static_assert(sizeof(Record) == 64, "one cache line per record");
+
+// The blend needs neither the rectangle test nor the alpha clamp for this
+// (view, Gaussian): no pixel outside the rectangle reaches alpha_min, and no
+// pixel alpha_max, with a margin far above float rounding.
+constexpr int kRecPlain = 1 << 15;
+__host__ __device__ __forceinline__ int rec_x_lo(int xword) { return xword & 0x7fff; }
 
 // Number of XCDs workgroups are dealt to round-robin (MI355X: 8).  Used to
 // give each XCD a contiguous range of tiles, so the records its L2 caches
@@ -190,7 +197,7 @@ __device__ __forceinline__ TileRect item_tile_rect(const Ws &ws, uint64_t val, i
     TileRect tr;
     if (!unpack_tile_rect((uint32_t)(val >> 32), tr)) {
         const int4 rc = ws.rec[(uint32_t)val].c;
-        tr.tx0 = (rc.z & 0xffff) / tile;
+        tr.tx0 = rec_x_lo(rc.z) / tile;
         tr.tx1 = (rc.z >> 16) / tile;
         tr.ty0 = (rc.w & 0xffff) / tile;
         tr.ty1 = (rc.w >> 16) / tile;

@@ -239,7 +239,21 @@ __global__ __launch_bounds__(kPreThreads) void k_preprocess(Ws ws, xg_gaussians 
             ra = make_float4((float)(ux - fx_), (float)(uy - fy_), (float)qa, (float)qb);
             // -log2(o) (+inf for o = 0: then every a is 0)
             rb = make_float4((float)qc, -log2f(o), g.intensity[i], __uint_as_float(dbits));
-            const int4 ci = make_int4((int)fx_, (int)fy_, ko.xl | (ko.xh << 16), ko.yl | (ko.yh << 16));
+            // kRecPlain: the box of the alpha >= alpha_min footprint, with its
+            // own opacity and slack (0.01 pixels and 1e-4 of the radius, far
+            // above the blend's float32 error), holds no pixel centre beyond
+            // the rectangle (pixels past the detector's edge do not exist),
+            // and the opacity stays below the clamp
+            const float reach = 2.0f * logf(o / p.alpha_min);
+            const double px_ = (double)(1.0001f * sqrtf(reach * (float)P.sxx) + 0.01f);
+            const double py_ = (double)(1.0001f * sqrtf(reach * (float)P.syy) + 0.01f);
+            const bool plain = o <= 0.98f && o <= 0.99f * p.alpha_max && P.sxx < 1e5 && P.syy < 1e5 &&
+                               (ko.xl == 0 || ux - px_ > (double)ko.xl - 0.5) &&
+                               (ko.xh == c.width - 1 || ux + px_ < (double)ko.xh + 1.5) &&
+                               (ko.yl == 0 || uy - py_ > (double)ko.yl - 0.5) &&
+                               (ko.yh == c.height - 1 || uy + py_ < (double)ko.yh + 1.5);
+            const int4 ci = make_int4((int)fx_, (int)fy_, ko.xl | (ko.xh << 16) | (plain ? kRecPlain : 0),
+                                      ko.yl | (ko.yh << 16));
             rc = make_float4(__int_as_float(ci.x), __int_as_float(ci.y), __int_as_float(ci.z),
                              __int_as_float(ci.w));
             const int T = p.tile;
