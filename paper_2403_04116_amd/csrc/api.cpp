@@ -385,7 +385,7 @@ xg_status xg_preprocess(const xg_frame *f, const xg_gaussians *g, void *stream) 
     hipStream_t s = (hipStream_t)stream;
     const Ws ws = resolve(f, P);
     const Params p = params_of(f->settings);
-    return hip_status(launch_preprocess(ws, *g, f->cams_dev, p, s));
+    return hip_status(launch_preprocess(ws, *g, f->cams_dev, p, false, s));
 }
 
 xg_status xg_bin_sort(const xg_frame *f, void *stream) {
@@ -429,7 +429,7 @@ xg_status xg_preprocess_rgb(const xg_frame *f, const xg_gaussians *g, const floa
     hipStream_t s = (hipStream_t)stream;
     const Ws ws = resolve(f, P);
     const Params p = params_of(f->settings);
-    hipError_t e = launch_preprocess(ws, *g, f->cams_dev, p, s);
+    hipError_t e = launch_preprocess(ws, *g, f->cams_dev, p, true, s);
     if (e == hipSuccess) e = launch_sh_color(ws, f->cams_dev, g->means, sh, degree, s);
     return hip_status(e);
 }

@@ -276,7 +276,7 @@ __device__ __forceinline__ void zero_item_sort(const Ws &ws, int64_t i) {
 
 // ---- launchers (one translation unit per stage) --------------------------
 hipError_t launch_preprocess(const Ws &ws, const xg_gaussians &g, const xg_camera *cams,
-                             const Params &p, hipStream_t s);
+                             const Params &p, bool colours, hipStream_t s);
 hipError_t launch_scan(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp,
                        int32_t *total, int32_t *status, int64_t cap, hipStream_t s);
 hipError_t launch_sort_items(const Ws &ws, const xg_camera *cams, const Params &p, hipStream_t s);

@@ -105,6 +105,21 @@ __device__ __forceinline__ bool key_view(const float *m, const float *M, float o
     return true;
 }
 
+// 1 / x and 1 / sqrt(x) of a positive normal x, to the last bits: the
+// hardware's estimate (about 24 bits) and two Newton steps, each doubling
+// them, in a third of the instructions of the IEEE sequences (what they feed
+// is rounded to float32).
+__device__ __forceinline__ double rcp64(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(r, fma(-x, r, 1.0), r);
+    return fma(r, fma(-x, r, 1.0), r);
+}
+__device__ __forceinline__ double rsqrt64(double x) {
+    double r = __builtin_amdgcn_rsq(x);
+    r = fma(0.5 * r, fma(-x * r, r, 1.0), r);
+    return fma(0.5 * r, fma(-x * r, r, 1.0), r);
+}
+
 // Rotation matrix of a unit quaternion (w, x, y, z), float64.
 __device__ __forceinline__ void quat_rot(const double q[4], double R[9]) {
     double w = q[0], x = q[1], y = q[2], z = q[3];
@@ -115,17 +130,15 @@ __device__ __forceinline__ void quat_rot(const double q[4], double R[9]) {
 
 // Float64 per-Gaussian part: the unit quaternion and its rotation matrix.
 struct Gauss64 {
-    double qn;          // norm of the input quaternion
+    double rqn;         // 1 / norm of the input quaternion
     double q[4];        // unit quaternion
     double R[9];
 };
 
 __device__ __forceinline__ void gauss64(const float *q, Gauss64 &G) {
     double q0 = q[0], q1 = q[1], q2 = q[2], q3 = q[3];
-    G.qn = sqrt(q0 * q0 + q1 * q1 + q2 * q2 + q3 * q3);
-    // one float64 reciprocal per divisor (the float32 results these feed
-    // are rounded once; the extra float64 rounding is far below that)
-    const double rqn = 1.0 / G.qn;
+    const double rqn = rsqrt64(q0 * q0 + q1 * q1 + q2 * q2 + q3 * q3);
+    G.rqn = rqn;
     G.q[0] = q0 * rqn; G.q[1] = q1 * rqn; G.q[2] = q2 * rqn; G.q[3] = q3 * rqn;
     quat_rot(G.q, G.R);
 }
@@ -148,7 +161,7 @@ __device__ __forceinline__ void project64(const float *m, const float *s, const 
     for (int a = 0; a < 3; ++a)
         P.t[a] = r[3 * a] * m[0] + r[3 * a + 1] * m[1] + r[3 * a + 2] * m[2] + (double)c.trans[a];
     double fx = c.fx, fy = c.fy, tz = P.t[2];
-    P.rtz = 1.0 / tz;
+    P.rtz = rcp64(tz);
     const double J00 = fx * P.rtz, J02 = -fx * P.t[0] * (P.rtz * P.rtz);
     const double J11 = fy * P.rtz, J12 = -fy * P.t[1] * (P.rtz * P.rtz);
     double A2[6];   // J W (the zeros of J left out)
@@ -181,11 +194,28 @@ __device__ __forceinline__ KeyOut key_path(const float *m, const float *s, const
     return out;
 }
 
+template <bool STREAM>
+__device__ __forceinline__ void store4(float4 *p, const float4 &v) {
+    using f32x4 = __attribute__((ext_vector_type(4))) float;
+    if (STREAM)
+        __builtin_nontemporal_store(f32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<f32x4 *>(p));
+    else
+        *p = v;
+}
+
 // One thread per (view, Gaussian), view-major, so each view's records are
 // written contiguously.  (Sharing the per-Gaussian part of the projection
 // across a workgroup's views through LDS measured slower: the lower
 // occupancy and the serial per-Gaussian phase cost more than the work it
 // saves.)
+//
+// STREAM: records and cleared gradients are stored past the caches
+// (nontemporal).  From about a million items they push out everything else
+// there, the sort's keys and values among it, before the blend reads them:
+// 1.6M items (200k x 8 views) 45 -> 42 us, 16M 451 -> 356 us and the sort's
+// histogram 28 -> 22.  Smaller frames are read back from the caches (0.8M
+// items: 4 us slower over the whole forward pass).
+template <bool STREAM>
 __global__ __launch_bounds__(kPreThreads) void k_preprocess(Ws ws, xg_gaussians g,
                                                             const xg_camera *cams, Params p,
                                                             uint32_t *depth_part) {
@@ -206,7 +236,7 @@ __global__ __launch_bounds__(kPreThreads) void k_preprocess(Ws ws, xg_gaussians 
     float4 ra = make_float4(0.f, 0.f, 0.f, 0.f), rb = ra, rc = ra;
     uint32_t dmin = 0xffffffffu, dmax = 0u;
     if (idx < ws.n_items) {
-        const int v = (int)(idx / ws.n);
+        const int v = (int)((uint32_t)idx / (uint32_t)ws.n);   // (fewer than 2^32 items)
         const int64_t i = idx - (int64_t)v * ws.n;
         const xg_camera &c = cams[v];
         const float *m = g.means + 3 * i;
@@ -225,10 +255,12 @@ __global__ __launch_bounds__(kPreThreads) void k_preprocess(Ws ws, xg_gaussians 
             double det = P.sxx * P.syy - P.sxy * P.sxy;
             const double k = (double)kLog2eHalf;
             // k d^T Sigma''^-1 d = (qa dx + qb dy)^2 + (qc dy)^2
-            const double rdet = 1.0 / det;
-            double qa = sqrt(k * P.syy * rdet);
-            double qb = -k * P.sxy * rdet / qa;
-            double qc = sqrt(k / P.syy);
+            const double krdet = k * rcp64(det);
+            const double qa2 = P.syy * krdet;
+            const double rqa = rsqrt64(qa2);
+            const double qa = qa2 * rqa;
+            const double qb = -P.sxy * krdet * rqa;
+            const double qc = rsqrt64(P.syy * (1.0 / k));
             double ux = (double)c.fx * P.t[0] * P.rtz + (double)c.cx;
             double uy = (double)c.fy * P.t[1] * P.rtz + (double)c.cy;
             double fx_ = floor(ux), fy_ = floor(uy);
@@ -255,9 +287,10 @@ __global__ __launch_bounds__(kPreThreads) void k_preprocess(Ws ws, xg_gaussians 
                                       ko.yl | (ko.yh << 16));
             rc = make_float4(__int_as_float(ci.x), __int_as_float(ci.y), __int_as_float(ci.z),
                              __int_as_float(ci.w));
-            const int T = p.tile;
-            count = (uint32_t)((ko.xh / T - ko.xl / T + 1) * (ko.yh / T - ko.yl / T + 1));
-            trect = pack_tile_rect(ko.xl / T, ko.xh / T, ko.yl / T, ko.yh / T);
+            const int sh = 31 - __clz(p.tile);   // tiles are 8, 16 or 32 pixels
+            const int tx0 = ko.xl >> sh, tx1 = ko.xh >> sh, ty0 = ko.yl >> sh, ty1 = ko.yh >> sh;
+            count = (uint32_t)((tx1 - tx0 + 1) * (ty1 - ty0 + 1));
+            trect = pack_tile_rect(tx0, tx1, ty0, ty1);
             dmin = dbits;
             dmax = dbits;
             key = dbits;
@@ -279,14 +312,14 @@ __global__ __launch_bounds__(kPreThreads) void k_preprocess(Ws ws, xg_gaussians 
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
             const int j = m * kPreThreads + threadIdx.x;   // float4 j of the range: record j/4, part j%4
-            if (j / 4 < nrec) out[j] = s_rec[j & 3][j >> 2];
+            if (j / 4 < nrec) store4<STREAM>(out + j, s_rec[j & 3][j >> 2]);
         }
         // clear the 2-D gradient accumulators (32 bytes per item) for the backward
         float4 *g2 = reinterpret_cast<float4 *>(ws.grad2d) + 2 * first;
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
             const int j = m * kPreThreads + threadIdx.x;
-            if (j / 2 < nrec) g2[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (j / 2 < nrec) store4<STREAM>(g2 + j, make_float4(0.f, 0.f, 0.f, 0.f));
         }
     }
     // block min/max of the kept depths -> one partial per block
@@ -421,12 +454,6 @@ __global__ __launch_bounds__(256) void k_emit(Ws ws, const xg_camera *cams, int 
 // took 330).  Each view's 2-D gradients are loaded one view ahead.  200k
 // Gaussians x 8 views: 33 -> 22 us; 1M x 16: 196 -> 143 us (670 MB).  (128
 // registers spill in the loop: 48 and 256 us.)
-__device__ __forceinline__ double rcp64(double x) {   // 1 / x of a positive normal x, to the last bits
-    double r = __builtin_amdgcn_rcp(x);               // about 24 bits; each step doubles them
-    r = fma(r, fma(-x, r, 1.0), r);
-    return fma(r, fma(-x, r, 1.0), r);
-}
-
 template <bool ACCUM>
 __global__ __launch_bounds__(256, 3) void k_preprocess_bwd(Ws ws, xg_gaussians g, const xg_camera *cams,
                                                         Params p, xg_grads gr) {
@@ -552,7 +579,7 @@ __global__ __launch_bounds__(256, 3) void k_preprocess_bwd(Ws ws, xg_gaussians g
         const double gz = 2 * (-2 * z * GR[0] - w * GR[1] + x * GR[2] + w * GR[3] - 2 * z * GR[4]
                                + y * GR[5] + x * GR[6] + y * GR[7]);
         const double dot = w * gw + x * gx + y * gy + z * gz;
-        const double rqn = 1.0 / G.qn;
+        const double rqn = G.rqn;
         gq[0] = (gw - w * dot) * rqn;
         gq[1] = (gx - x * dot) * rqn;
         gq[2] = (gy - y * dot) * rqn;
@@ -597,6 +624,8 @@ __global__ __launch_bounds__(256) void k_fill_u32(uint32_t *p, uint32_t v, int64
         p[k] = v;
 }
 
+constexpr int64_t kStreamItems = 1 << 20;
+
 int grid_for(int64_t n, int threads, int max_blocks = 65536) {
     int64_t b = (n + threads - 1) / threads;
     if (b < 1) b = 1;
@@ -607,17 +636,19 @@ int grid_for(int64_t n, int threads, int max_blocks = 65536) {
 }  // namespace
 
 
+// colours: the records' fourth slots are written right after
 hipError_t launch_preprocess(const Ws &ws, const xg_gaussians &g, const xg_camera *cams,
-                             const Params &p, hipStream_t s) {
+                             const Params &p, bool colours, hipStream_t s) {
     const int64_t nb = (ws.n_items + kPreThreads - 1) / kPreThreads;
     if (nb > 0x7fffffff) return hipErrorInvalidValue;
     // depth partials live in the scan scratch: the item sort's first launch
     // reduces them into the header (and resets it for the frame) before
     // anything else uses that scratch
     uint32_t *part = ws.scan_tmp;
-    if (nb > 0)
-        hipLaunchKernelGGL(k_preprocess, dim3((unsigned)nb), dim3(kPreThreads), 0, s, ws, g, cams, p,
-                           part);
+    if (nb > 0 && ws.n_items >= kStreamItems && !colours)
+        hipLaunchKernelGGL(k_preprocess<true>, dim3((unsigned)nb), dim3(kPreThreads), 0, s, ws, g, cams, p, part);
+    else if (nb > 0)
+        hipLaunchKernelGGL(k_preprocess<false>, dim3((unsigned)nb), dim3(kPreThreads), 0, s, ws, g, cams, p, part);
     else
         hipLaunchKernelGGL(k_header_reset, dim3(1), dim3(64), 0, s, ws.hdr);
     return hipGetLastError();
