@@ -278,10 +278,13 @@ __device__ __forceinline__ void stage(const Ws &ws, const uint32_t *vals, uint32
 // Compacts, in list order, the staged entries [0, cnt) whose rectangle
 // touches this wavefront's sub-block w into list[]; returns their number
 // (wavefront-uniform).  An entry k is stored as 16 k, the byte offset of its
-// slot in the float4 record arrays (k < B <= 256, so 16 k fits 16 bits), and
-// the blend loops read records without scaling the index.  exact: one of the
-// entries needs the rectangle test and the alpha clamp.
-__device__ __forceinline__ int wave_list(const uint16_t *s_mask, int cnt, int w, uint16_t *list, bool &exact) {
+// slot in the float4 record arrays, and the blend loops read records without
+// scaling the index.  The kListPad words after the last entry name the empty
+// slot.  exact: one of the entries needs the rectangle test and the alpha
+// clamp.
+constexpr int kListPad = 8;
+template <int B>
+__device__ __forceinline__ int wave_list(const uint16_t *s_mask, int cnt, int w, uint32_t *list, bool &exact) {
     const int lane = lane_id();
     const uint64_t lt = (1ull << lane) - 1ull;
     int n = 0;
@@ -292,9 +295,10 @@ __device__ __forceinline__ int wave_list(const uint16_t *s_mask, int cnt, int w,
         const bool sel = (m >> w) & 1u;
         const uint64_t bal = __ballot(sel);
         ex |= __ballot(sel && (m & kMaskExact));
-        if (sel) list[n + __popcll(bal & lt)] = (uint16_t)(16 * k);
+        if (sel) list[n + __popcll(bal & lt)] = 16u * (uint32_t)k;
         n += __popcll(bal);
     }
+    if (lane < kListPad) list[n + lane] = 16u * B;
     exact = ex != 0;
     return n;
 }
@@ -304,22 +308,33 @@ __device__ __forceinline__ float4 slot16(const float4 *base, uint32_t off) {
     return *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(base) + off);
 }
 
-// LDS of one blending workgroup (the forward leaves rid and wmax unused;
+// LDS of one blending workgroup (rid and wmax: the backward's;
 // c holds the staged RGB colours of the CH = 3 forward, cmask the culled
 // sub-block masks of the counting forward).
-template <int T, int B, int CH = 1, bool CNT = false>
+template <int T, int B, bool BWD = false, int CH = 1, bool CNT = false>
 struct BlendLds {
     static constexpr int NW = T * T / kWave;
-    float4 a[B];
-    float4 b[B];
-    float4 c[CH == 3 ? B : 1];
-    uint32_t rid[4 * B];   // record index of entry k at rid[4 k] (read at the entry's byte offset)
+    // slot B is the empty one (empty_slot)
+    float4 a[B + 1];
+    float4 b[B + 1];
+    float4 c[CH == 3 ? B + 1 : 1];
+    uint32_t rid[BWD ? 4 * (B + 1) : 1];   // record index of entry k at rid[4 k] (read at the entry's byte offset)
     uint16_t mask[B];
-    uint16_t cmask[CNT ? B : 1];
-    alignas(16) uint16_t list[NW][B];
+    uint16_t cmask[CNT ? B + 1 : 1];
+    alignas(16) uint32_t list[NW][B + kListPad];
     int wmax[NW];
     int next;
 };
+
+// The record that fills the blend loops' last group of entries: no pixel
+// takes it.  Its exponent is NaN, so its alpha passes no comparison with
+// alpha_min (0 included), and where the clamp would turn that into alpha_max,
+// the rectangle covers no pixel.
+template <int T, typename Lds>
+__device__ __forceinline__ void empty_slot(Lds &sh, int B) {
+    sh.a[B] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    sh.b[B] = make_float4(0.0f, __builtin_nanf(""), 0.0f, __uint_as_float(T <= 16 ? 0u : 255u));
+}
 
 // CH = 1: the radiative intensity of the record (Eq. 10).  CH = 3: the
 // three colour channels of the record's fourth slot (the comparison model),
@@ -333,9 +348,8 @@ template <int T, int B, bool COUNT, bool STORE, int CH = 1>
 __device__ __forceinline__ void fwd_tile(int tile, const Ws &ws, const xg_camera *cams,
                                          const Params &p, float *image, float *final_t,
                                          int32_t *n_contrib, int32_t *counts, const TStore &ts,
-                                         const L1Fuse &l1, BlendLds<T, B, CH, COUNT> &sh) {
+                                         const L1Fuse &l1, BlendLds<T, B, false, CH, COUNT> &sh) {
     static_assert(CH == 1 || (CH == 3 && !COUNT && !STORE), "RGB forward: plain variant only");
-    static_assert(B % 8 == 0, "list groups of 8 are read 16 bytes at a time");
     constexpr int NT = T * T;
     constexpr int SB = T / 8;
     float4 *s_a = sh.a;
@@ -357,58 +371,59 @@ __device__ __forceinline__ void fwd_tile(int tile, const Ws &ws, const xg_camera
     const uint32_t e = ws.ranges[2 * (int64_t)tile + 1];
     const uint32_t *vals = ws.pair_vals;
     const float amin = p.alpha_min, amax = p.alpha_max, tmin = p.t_min;
-    uint16_t *list = sh.list[w];
+    const uint32_t *list = sh.list[w];
 
     float Tr = 1.0f, C = 0.0f, Cg = 0.0f, Cb = 0.0f;
     int last = 0;
     // counting variant: per lane (rows 0-2, 6, 7) and per wavefront (3-5)
     int n_eval = 0, n_con = 0, n_upto = 0, n_fev = 0, n_bev = 0, bev_run = 0;
     int w_red = 0, w_bvis = 0, w_fvis = 0, w_cvis = 0;
-    bool done = !inside;
+    if (threadIdx.x == 0) {
+        empty_slot<T>(sh, B);
+        if (COUNT) sh.cmask[B] = 0;
+    }
+    uint64_t live = __ballot(inside);   // lanes that have not terminated
     int nc = 0;   // contributors so far (stored variant)
     float *tbase = STORE ? ts.t + (int64_t)tile * ts.slots * NT + threadIdx.x : nullptr;
     for (uint32_t b0 = s; b0 < e; b0 += B) {
         const int cnt = (int)min((uint32_t)B, e - b0);
-        if (!__syncthreads_or(!done)) break;
+        if (!__syncthreads_or(live != 0)) break;
         // the counting variant keeps every rectangle evaluation (the work
         // count of the definition), the others skip sub-blocks out of reach
         stage<T, NT, !COUNT, COUNT, (COUNT || CH == 3) ? 0 : 1>(ws, vals, b0, cnt, tg, amin, s_a, s_b, s_mask, nullptr,
                                     CH == 3 ? sh.c : nullptr, COUNT ? sh.cmask : nullptr);
         __syncthreads();
-        if (!__any(!done)) continue;
+        if (live == 0) continue;
         bool exact;
-        const int nl = wave_list(s_mask, cnt, w, list, exact);
+        const int nl = wave_list<B>(s_mask, cnt, w, sh.list[w], exact);
         exact = exact || T > 16 || COUNT;
         int lk = -1;   // 16 x batch index of this lane's last contributor in the batch
-        // one entry at byte offset `off` (16 x its batch index) of the record
-        // arrays; plain: every record of the wavefront's list is marked
-        // kRecPlain, so the rectangle test and the clamp change nothing
-        auto blend = [&](auto plain, uint32_t off, const float4 &sa, const float4 &sb) {
-            constexpr bool PLAIN = decltype(plain)::value;
-            const float4 sc = CH == 3 ? slot16(sh.c, off) : sb;
-            const bool inr = PLAIN || in_rect<T>(__float_as_uint(sb.w), rkey, lx, ly);
-            const bool act = !done && inr;
-            const bool live = COUNT && __any(!done);   // before this entry
-            const Eval ev = splat_eval<PLAIN>(sa, sb, pxr, pyr, amax);
-            const bool con = act && ev.alpha >= amin;
+        // the entry at byte offset `off` (16 x its batch index) of the record
+        // arrays, with its evaluation and its colour; inr: the lanes whose
+        // pixel the rectangle holds
+        auto composite = [&](uint32_t off, uint64_t inr, const Eval &ev, float c0, float c1, float c2) {
+            const uint64_t act_m = live & inr;
+            const bool any_live = live != 0;   // before this entry
+            const uint64_t con = act_m & __ballot(ev.alpha >= amin);
             const float Tn = fmaf(-Tr, ev.alpha, Tr);   // T (1 - alpha), one rounding
-            const bool term = con && Tn < tmin;
-            const bool keep = con != term;   // con and not term (term implies con)
-            done = done || term;
+            const uint64_t keep_m = con & __ballot(!(Tn < tmin));
+            const bool keep = __builtin_amdgcn_inverse_ballot_w64(keep_m);
+            live &= ~(con ^ keep_m);   // con without keep: the lane terminates
             if (STORE) {
                 if (keep && nc < ts.slots) tbase[(int64_t)nc * NT] = Tr;
                 nc += keep ? 1 : 0;
             }
             if constexpr (CH == 3) {
-                C = keep ? fmaf(sc.x * ev.alpha, Tr, C) : C;
-                Cg = keep ? fmaf(sc.y * ev.alpha, Tr, Cg) : Cg;
-                Cb = keep ? fmaf(sc.z * ev.alpha, Tr, Cb) : Cb;
+                C = keep ? fmaf(c0 * ev.alpha, Tr, C) : C;
+                Cg = keep ? fmaf(c1 * ev.alpha, Tr, Cg) : Cg;
+                Cb = keep ? fmaf(c2 * ev.alpha, Tr, Cb) : Cb;
             } else {
-                C = keep ? fmaf(sb.z * ev.alpha, Tr, C) : C;
+                C = keep ? fmaf(c0 * ev.alpha, Tr, C) : C;
             }
             Tr = keep ? Tn : Tr;
             lk = keep ? (int)off : lk;
             if (COUNT) {
+                const bool act = __builtin_amdgcn_inverse_ballot_w64(act_m);
                 n_eval += act ? 1 : 0;
                 n_con += keep ? 1 : 0;
                 n_upto = keep ? n_eval : n_upto;
@@ -416,59 +431,62 @@ __device__ __forceinline__ void fwd_tile(int tile, const Ws &ws, const xg_camera
                 w_red += any_keep ? 1 : 0;
                 if ((sh.cmask[off >> 4] >> w) & 1u) {   // an entry the blend kernels visit
                     ++w_cvis;
-                    if (live) {
+                    if (any_live) {
                         ++w_fvis;
                         n_fev += act ? 1 : 0;
                     }
-                    bev_run += inr ? 1 : 0;
+                    bev_run += __builtin_amdgcn_inverse_ballot_w64(inr) ? 1 : 0;
                     if (any_keep) w_bvis = w_cvis;
                     n_bev = keep ? bev_run : n_bev;
                 }
             }
         };
-        // groups of 8 entries, their indices in one 16-byte read (in the row:
-        // j0 is a multiple of 8 and B of 8); the wavefront leaves the batch
-        // after a group once all its lanes have terminated.  A full group has
-        // no test between its entries, and each entry's record is loaded one
-        // entry ahead of its use (the barrier keeps the scheduler from moving
-        // the loads back down): a few scalar instructions and two branches
-        // fewer an entry, and no LDS latency on a wavefront that is alone on
-        // its SIMD.  Measured: ACUI scan of 100 views of 512 x 512 1.51 -> 1.47
-        // ms, 50k Gaussians in one 256 x 256 view (one wavefront a SIMD) 205 ->
-        // 174 us a step.
+        // plain: every record of the wavefront's list is marked kRecPlain, so
+        // the rectangle test and the clamp change nothing
         auto walk = [&](auto plain) {
-            int j0 = 0;
-            // (not for three channels, whose records take too many registers)
-            for (; CH == 1 && j0 + 8 <= nl; j0 += 8) {
-                const uint4 idx8 = *reinterpret_cast<const uint4 *>(list + j0);
-                const uint32_t iw[4] = {idx8.x, idx8.y, idx8.z, idx8.w};
-                uint32_t off_n = iw[0] & 0xffffu;
-                float4 sa_n = slot16(s_a, off_n), sb_n = slot16(s_b, off_n);
+            constexpr bool PLAIN = decltype(plain)::value;
+            auto covers = [&](const float4 &sb) {
+                return PLAIN ? ~0ull : __ballot(in_rect<T>(__float_as_uint(sb.w), rkey, lx, ly));
+            };
+            // Groups of 4 entries, their offsets in one 16-byte read, the last
+            // group filled up with the empty slot (no test between entries);
+            // the wavefront leaves the batch after a group once all its lanes
+            // have terminated.  Each entry's record is loaded one entry ahead
+            // of its use, also from one group to the next (the read after the
+            // last group stays in the row's padding; the barrier keeps the
+            // scheduler from moving the loads back down).  A visit is 16 VALU
+            // instructions and, the lane masks being kept as scalar words
+            // rather than lane booleans, 4 scalar ones; with 16-bit offsets to
+            // unpack, a tested partial group and booleans it was 17 and 5.  A
+            // wavefront alone on its SIMD issues an instruction every 6 cycles
+            // or so and gains most.  Measured (with the same groups in the
+            // backward): one view of 50k Gaussians at 256 x 256, a step 168 ->
+            // 159 us; 1M x 16 views 2.29 -> 2.25 ms; ACUI scan of 100 views 1.35 ->
+            // 1.32 ms; three channels, 200k x 4 views 220 -> 215 us.  Computing
+            // the next entry's alpha beside the current entry's update, to
+            // hide the exponential's latency, gained nothing.
+            if (nl == 0) return;
+            uint4 q = *reinterpret_cast<const uint4 *>(list);
+            float4 sa_n = slot16(s_a, q.x), sb_n = slot16(s_b, q.x);
+            auto group = [&](const uint4 &g, uint32_t next) {
+                const uint32_t off[5] = {g.x, g.y, g.z, g.w, next};
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const uint32_t off = off_n;
+                for (int u = 0; u < 4; ++u) {
                     const float4 sa = sa_n, sb = sb_n;
-                    if (u < 7) {   // one entry ahead
-                        off_n = (iw[(u + 1) >> 1] >> (16 * ((u + 1) & 1))) & 0xffffu;
-                        sa_n = slot16(s_a, off_n);
-                        sb_n = slot16(s_b, off_n);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                    blend(plain, off, sa, sb);
+                    sa_n = slot16(s_a, off[u + 1]);
+                    sb_n = slot16(s_b, off[u + 1]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    const float4 sc = CH == 3 ? slot16(sh.c, off[u]) : make_float4(sb.z, 0.0f, 0.0f, 0.0f);
+                    composite(off[u], covers(sb), splat_eval<PLAIN>(sa, sb, pxr, pyr, amax), sc.x, sc.y, sc.z);
                 }
-                if (!__any(!done)) break;
-            }
-            // the partial group that is left (three channels: every group), with a
-            // wavefront-uniform test between its entries
-            for (; j0 < nl && __any(!done); j0 += 8) {
-                const uint4 idx8 = *reinterpret_cast<const uint4 *>(list + j0);
-                const uint32_t iw[4] = {idx8.x, idx8.y, idx8.z, idx8.w};
-#pragma unroll
-                for (int u = 0; u < (CH == 1 ? 7 : 8); ++u) {
-                    if (j0 + u >= nl) break;
-                    const uint32_t off = (iw[u >> 1] >> (16 * (u & 1))) & 0xffffu;
-                    blend(plain, off, slot16(s_a, off), slot16(s_b, off));
-                }
+            };
+            for (int j0 = 4;; j0 += 8) {
+                const uint4 q1 = *reinterpret_cast<const uint4 *>(list + j0);
+                group(q, q1.x);
+                if (j0 >= nl || live == 0) break;
+                q = *reinterpret_cast<const uint4 *>(list + j0 + 4);
+                group(q1, q.x);
+                if (j0 + 4 >= nl || live == 0) break;
             }
         };
         if (exact)
@@ -539,12 +557,13 @@ __device__ __forceinline__ void finish_queue(int32_t *queue, int32_t *done) {
 // tiles from the work queue; otherwise one workgroup per tile.
 // STORE = true: also keep the transmittance before each of the first
 // ts.slots contributors of every pixel (one workgroup per tile only).
+// (64 registers: as for the backward below)
 template <int T, int B, bool COUNT, bool PERSIST, bool STORE>
-__global__ __launch_bounds__(T * T) void k_render_fwd(Ws ws, const xg_camera *cams, Params p,
+__global__ __launch_bounds__(T * T, T > 8 && !PERSIST && !STORE && !COUNT ? 8 : 2) void k_render_fwd(Ws ws, const xg_camera *cams, Params p,
                                                       float *image, float *final_t,
                                                       int32_t *n_contrib, int32_t *counts,
                                                       TStore ts, L1Fuse l1) {
-    __shared__ BlendLds<T, B, 1, COUNT> sh;
+    __shared__ BlendLds<T, B, false, 1, COUNT> sh;
     if (!PERSIST) {
         fwd_tile<T, B, COUNT, STORE>(ordered_tile(ws.blend_order, blockIdx.x, (int)ws.total_tiles), ws, cams, p, image,
                                      final_t, n_contrib, counts, ts, l1, sh);
@@ -561,10 +580,10 @@ __global__ __launch_bounds__(T * T) void k_render_fwd(Ws ws, const xg_camera *ca
 // Forward of the comparison model: three colour channels per pixel, one
 // workgroup per tile.
 template <int T, int B>
-__global__ __launch_bounds__(T * T) void k_render_fwd_rgb(Ws ws, const xg_camera *cams, Params p,
+__global__ __launch_bounds__(T * T, T > 8 ? 8 : 2) void k_render_fwd_rgb(Ws ws, const xg_camera *cams, Params p,
                                                           float *image, float *final_t,
                                                           int32_t *n_contrib) {
-    __shared__ BlendLds<T, B, 3> sh;
+    __shared__ BlendLds<T, B, false, 3> sh;
     fwd_tile<T, B, false, false, 3>(ordered_tile(ws.blend_order, blockIdx.x, (int)ws.total_tiles), ws, cams, p, image,
                                     final_t, n_contrib, nullptr, TStore{nullptr, nullptr, 0},
                                     L1Fuse{nullptr, nullptr, 0.0f}, sh);
@@ -646,12 +665,10 @@ template <int T, int B, bool STORE>
 __device__ __forceinline__ void bwd_tile(int tile, const Ws &ws, const xg_camera *cams,
                                          const Params &p, const float *dl_dimage,
                                          const float *final_t, const int32_t *n_contrib,
-                                         const TStore &ts, BlendLds<T, B> &sh) {
+                                         const TStore &ts, BlendLds<T, B, true> &sh) {
     constexpr int NT = T * T;
     constexpr int NW = NT / kWave;
     constexpr int SB = T / 8;
-    static_assert(B % 8 == 0, "list groups of 8 are read 16 bytes at a time");
-    static_assert((B & (B - 1)) == 0 && B <= 256, "list offsets are masked to 16 (B - 1) in 16 bits");
     float4 *s_a = sh.a;
     float4 *s_b = sh.b;
     uint32_t *s_rid = sh.rid;
@@ -672,7 +689,7 @@ __device__ __forceinline__ void bwd_tile(int tile, const Ws &ws, const xg_camera
     const uint32_t s = ws.ranges[2 * (int64_t)tile];
     const uint32_t *vals = ws.pair_vals;
     const float amin = p.alpha_min, amax = p.alpha_max;
-    uint16_t *list = sh.list[w];
+    const uint32_t *list = sh.list[w];
 
     float g = 0.0f, Tr = 1.0f;
     int last = 0;
@@ -696,6 +713,7 @@ __device__ __forceinline__ void bwd_tile(int tile, const Ws &ws, const xg_camera
     int wmax = last;
     for (int off = kWave / 2; off > 0; off >>= 1) wmax = max(wmax, __shfl_xor(wmax, off, kWave));
     if (lane == 0) s_max[w] = wmax;
+    if (threadIdx.x == 0) empty_slot<T>(sh, B);
     __syncthreads();
     int bmax = 0;
 #pragma unroll
@@ -720,50 +738,35 @@ __device__ __forceinline__ void bwd_tile(int tile, const Ws &ws, const xg_camera
         __syncthreads();
         if (b0 >= wmax) continue;
         bool exact;
-        const int nl = wave_list(s_mask, min(cnt, wmax - b0), w, list, exact);
+        const int nl = wave_list<B>(s_mask, min(cnt, wmax - b0), w, sh.list[w], exact);
         // 16 x batch index of this lane's last contributor (-16: none in the batch)
         const int lastk16 = 16 * max(last - b0 - 1, -1);
         // (plain: as in the forward)
         auto walk = [&](auto plain) {
             constexpr bool PLAIN = decltype(plain)::value;
-            // groups of 8 entries from the back, each group's indices in one
-            // 16-byte read (j0 is a multiple of 8 and B of 8, so the read stays in
-            // the row); entries past nl are skipped by a wavefront-uniform test
-            for (int j0 = (nl - 1) & ~7; j0 >= 0; j0 -= 8) {
-              const uint4 idx8 = *reinterpret_cast<const uint4 *>(list + j0);
-              const uint32_t iw[4] = {idx8.x, idx8.y, idx8.z, idx8.w};
-              // Each entry's record is loaded one entry ahead of its use.  Entries
-              // past nl are loaded too (and skipped): the offset is masked to a
-              // multiple of 16 below 16 B, which keeps every valid entry and keeps
-              // whatever the row holds past nl (earlier batches, or LDS never
-              // written) inside the record arrays.
-              constexpr uint32_t kOffMask = 16u * (B - 1);
-              uint32_t off_n = (iw[3] >> 16) & kOffMask;
-              float4 sa_n = slot16(s_a, off_n);
-              float4 sb_n = slot16(s_b, off_n);
+            // groups of G entries from the back, each group's offsets in one
+            // 16-byte read; the last is filled up with the empty slot.  Each
+            // entry's record is loaded one entry ahead of its use.
+            if (nl == 0) return;
+            int j0 = (nl - 1) & ~(G - 1);
+            uint4 q = *reinterpret_cast<const uint4 *>(list + j0);
+            float4 sa_n = slot16(s_a, q.w), sb_n = slot16(s_b, q.w);
+            for (;;) {
+              const uint32_t eoff = list[j0 + lane_e];   // the group's entry of this lane, for the sums
+              const int jn = j0 - G;
+              const uint4 qn = *reinterpret_cast<const uint4 *>(list + max(jn, 0));
+              const uint32_t offs[G] = {q.x, q.y, q.z, q.w};
               uint32_t live = 0;   // entries of the group that some lane contributes to (bit e)
-              uint32_t eoff = 0, rid = 0;
-              float eux = 0.0f;
               float acc[G][4];     // gp, gp dy, gp dy^2 and w of the group's entries
 #pragma unroll
-              for (int u = 7; u >= 0; --u) {
-                const int e = u & (G - 1);
-                // the group's entry of this lane, for the sums after its last entry
-                if (e == G - 1) eoff = list[j0 + (u & ~(G - 1)) + lane_e] & kOffMask;
-                if (e == G - 2) {
-                    eux = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(s_a) + eoff);
-                    rid = *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(s_rid) + eoff);
-                }
-                const uint32_t off = off_n;   // 16 x batch index
+              for (int e = G - 1; e >= 0; --e) {
+                const uint32_t off = offs[e];   // 16 x batch index
                 const float4 sa = sa_n;
                 const float4 sb = sb_n;
-                if (u > 0) {
-                    off_n = (iw[(u - 1) >> 1] >> (16 * ((u - 1) & 1))) & kOffMask;
-                    sa_n = slot16(s_a, off_n);
-                    sb_n = slot16(s_b, off_n);
-                }
-                const bool inr = j0 + u < nl && (int)off <= lastk16 &&
-                                 (PLAIN || in_rect<T>(__float_as_uint(sb.w), rkey, lx, ly));
+                const uint32_t off_n = e > 0 ? offs[e - 1] : qn.w;
+                sa_n = slot16(s_a, off_n);
+                sb_n = slot16(s_b, off_n);
+                const bool inr = (int)off <= lastk16 && (PLAIN || in_rect<T>(__float_as_uint(sb.w), rkey, lx, ly));
                 const Eval ev = splat_eval<PLAIN>(sa, sb, pxr, pyr, amax);
                 const bool act = inr && ev.alpha >= amin;
                 if (__any(act)) {
@@ -814,21 +817,25 @@ __device__ __forceinline__ void bwd_tile(int tile, const Ws &ws, const xg_camera
 #pragma unroll
                     for (int q = 0; q < 4; ++q) acc[e][q] = 0.0f;
                 }
-                if (e == 0 && live != 0) {
-                    float c2[2];
-                    row_sums(acc, lane, c2);
-                    const float x = column_sums(c2, pxr - eux, lane);
-                    if (live & lane_bit) {
-                        if (small_rid) {   // 32-bit byte offset from the array base
-                            atomicAdd(reinterpret_cast<float *>(reinterpret_cast<char *>(ws.grad2d) + (rid << 5 | lane_q4)), x);
-                        } else {
-                            atomicAdd(ws.grad2d + 8 * (int64_t)rid + lane_q, x);
-                            __asm__ volatile("" ::: "memory");   // keeps the two atomics apart
-                        }
+              }
+              if (live != 0) {
+                const float eux = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(s_a) + eoff);
+                const uint32_t rid = *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(s_rid) + eoff);
+                float c2[2];
+                row_sums(acc, lane, c2);
+                const float x = column_sums(c2, pxr - eux, lane);
+                if (live & lane_bit) {
+                    if (small_rid) {   // 32-bit byte offset from the array base
+                        atomicAdd(reinterpret_cast<float *>(reinterpret_cast<char *>(ws.grad2d) + (rid << 5 | lane_q4)), x);
+                    } else {
+                        atomicAdd(ws.grad2d + 8 * (int64_t)rid + lane_q, x);
+                        __asm__ volatile("" ::: "memory");   // keeps the two atomics apart
                     }
-                    live = 0;
                 }
               }
+              if (jn < 0) break;
+              j0 = jn;
+              q = qn;
             }
         };
         if (exact || T > 16)
@@ -844,7 +851,7 @@ template <int T, int B, bool PERSIST, bool STORE>
 __global__ __launch_bounds__(T * T, T > 8 && !PERSIST && !STORE ? 8 : 2) void k_render_bwd(Ws ws, const xg_camera *cams, Params p,
                                                       const float *dl_dimage, const float *final_t,
                                                       const int32_t *n_contrib, TStore ts) {
-    __shared__ BlendLds<T, B> sh;
+    __shared__ BlendLds<T, B, true> sh;
     if (!PERSIST) {
         bwd_tile<T, B, STORE>(ordered_tile(ws.blend_order, blockIdx.x, (int)ws.total_tiles), ws, cams, p, dl_dimage,
                               final_t, n_contrib, ts, sh);
