@@ -19,7 +19,7 @@
 //   3. k_bin_starts: the exclusive scan of a view's tile totals from the
 //      view's first pair slot -> the tile ranges [start, end);
 //   4. k_bin_scatter: per partition, the pairs in windows of kBinWindow
-//      slots: emitted into LDS in slot order, ranked stably within the
+//      slots: a lane finds its slot's pair, the pairs are ranked stably within the
 //      window (each row of 64 slots matched by tile through an LDS table of
 //      lane masks, per-wavefront counters, then a prefix over the
 //      wavefronts), reordered in LDS so that each tile's pairs are
@@ -267,7 +267,8 @@ __global__ __launch_bounds__(kStartThreads) void k_bin_starts(Ws ws, const xg_ca
 // Stable ranking and placement of one partition's pairs in one band of its
 // view's tile rows (LT tiles at most; most views have a single band).  The
 // pairs of the band are numbered in item order (slots).  Per window: the
-// pairs of slots [w0, w0 + kBinWindow) are emitted into LDS in slot order;
+// slots [w0, w0 + kBinWindow) at which items begin are marked, and each lane
+// counts its way to its slot's item, whose rectangle gives the pair's tile;
 // wavefront w ranks its kBinWindow / NW consecutive slots, row by row (the
 // lanes of a row holding a tile found through the lane-mask table), with a
 // 16-bit counter per tile (two per word, LDS atomics from one leader lane
@@ -282,6 +283,13 @@ __global__ __launch_bounds__(kStartThreads) void k_bin_starts(Ws ws, const xg_ca
 // Bands of 4096 tiles, whose counters leave 8 wavefronts on a CU: 200k
 // Gaussians, 8 views of 4096 tiles, 0.64 ms a forward pass where bands of 1024
 // take 0.52.)
+// What bounds it: barriers and LDS round trips with two workgroups on a CU
+// (HBM and VALU are both below half).  A lane per slot, loads issued together at the
+// start and one base word per tile for the placement, against a thread per item
+// that wrote its pairs one by one: ACUI scan of 100 views
+// (17 pairs an item) 1.355 -> 1.320 ms, one 2048 x 1536 view of 200k Gaussians 0.396 -> 0.375,
+// 200k x 8 views 0.468 -> 0.464, 1M x 16 views 2.31 -> 2.28; 1k Gaussians at
+// 64 x 64, which is all latency, 42.8 -> 43.1 us.
 // MI = items per thread: the partitions hold at most MI NT items.
 template <int MI>
 __global__ __launch_bounds__(1024, 8) void k_bin_scatter(Ws ws, const xg_camera *cams, int tile, int bands) {
@@ -292,19 +300,30 @@ __global__ __launch_bounds__(1024, 8) void k_bin_scatter(Ws ws, const xg_camera 
     constexpr int kMyItems = MI;
     static_assert(LT <= (1 << LB) && kBinWindow % NT == 0, "shape");
     static_assert(kBinWindow <= 65535, "window offsets and counts fit 16 bits");
-    __shared__ uint32_t h16[NW][LT / 2];
+    __shared__ alignas(16) uint32_t h16[NW][LT / 2];
     __shared__ uint32_t base[LT];
-    __shared__ uint16_t s_lt[kBinWindow];
-    __shared__ uint32_t s_gi[kBinWindow];
-    // the window's slots in tile order (slot of each window position), and
-    // each tile's first window position (two 16-bit starts per word)
-    __shared__ uint16_t s_perm[kBinWindow];
+    // the items with pairs in the band, in order: first tile | columns << 16 |
+    // first slot << 32
+    static_assert(LT <= 1 << 10, "fields of an item");
+    __shared__ uint64_t s_item[MI * NT];
+    // the slots of a window at which an item begins, a word for each row of 64
+    __shared__ uint64_t s_begin[2][kBinWindow / kWave];
+    static_assert(kBinWindow / kWave == kWave, "one word per lane");
+    // the window's pairs in tile order, and each tile's first window position
+    // (two 16-bit starts per word)
+    __shared__ alignas(16) uint32_t s_gi[kBinWindow];
+    __shared__ alignas(16) uint16_t s_lt[kBinWindow];
     __shared__ alignas(16) uint32_t s_lst[LT / 2];
     __shared__ uint32_t s_alloc;
     // ranking: per wavefront, a 64-bit lane mask for each value of a tile's
-    // low kHashBits bits (zero between rows)
+    // low kHashBits bits (zero between rows), in the words that hold the
+    // window's pairs afterwards
     constexpr int kHashBits = 6, kHash = 1 << kHashBits;
-    __shared__ uint64_t s_tab[NW][kHash];
+    static_assert(kHash == kWave && sizeof(s_gi) >= NW * kHash * sizeof(uint64_t), "one word per lane");
+    uint64_t *s_tab = reinterpret_cast<uint64_t *>(s_gi) + threadIdx.x / kWave * kHash;
+    // the items' indices, until the window's tiles take their words
+    static_assert(sizeof(s_lt) >= MI * NT * sizeof(uint32_t), "a word per item");
+    uint32_t *s_igi = reinterpret_cast<uint32_t *>(s_lt);
 
     // the first kXcds workgroups write the blend launches' tile order (the
     // ranges are final; every status, since the blends read it even when
@@ -315,125 +334,151 @@ __global__ __launch_bounds__(1024, 8) void k_bin_scatter(Ws ws, const xg_camera 
         return;
     }
     const int part = ((int)blockIdx.x - kXcds) / bands;
-    if (ws.hdr->status != XG_OK) return;
     const BinPart b = bin_part(ws, cams, tile, part);
     const Band bd(b, (int)blockIdx.x - kXcds - part * bands, LT);
     if (b.j0 >= b.j1 || bd.tiles <= 0) return;
 
-    for (int k = threadIdx.x; k < NW * kHash; k += NT) (&s_tab[0][0])[k] = 0ull;
+    // everything that depends on no other load is loaded before anything is
+    // used: two round trips to memory before the first window, where testing
+    // each in turn took five
+    const uint32_t status = ws.hdr->status;
+    const int sel = __builtin_amdgcn_readfirstlane((int)ws.hdr->item_sel) & 1;
+    const uint32_t pstart = ws.bin_pstart[part];
+    const int64_t j0 = b.j0 + (int64_t)threadIdx.x * kMyItems;   // this thread's items
+    uint32_t icnt[kMyItems];
+#pragma unroll
+    for (int k = 0; k < kMyItems; ++k) icnt[k] = j0 + k < b.j1 ? ws.icounts[j0 + k] : 0u;
     const uint32_t *colp = ws.bin_cnt + (int64_t)part * ws.bin_tiles + bd.first;
-    for (int t = threadIdx.x; t < bd.tiles; t += NT)
-        base[t] = ws.ranges[2 * ((int64_t)b.toff + bd.first + t)] + colp[t];
+    static_assert(LT == NT, "a tile per thread");
+    const bool mine = (int)threadIdx.x < bd.tiles;
+    const uint32_t tstart = mine ? ws.ranges[2 * ((int64_t)b.toff + bd.first + threadIdx.x)] : 0u;
+    const uint32_t tcol = mine ? colp[threadIdx.x] : 0u;
+    uint64_t ival[kMyItems];
+#pragma unroll
+    for (int k = 0; k < kMyItems; ++k) ival[k] = j0 + k < b.j1 ? ws.ivals[sel][j0 + k] : 0ull;
+    if (status != XG_OK) return;
+    if (threadIdx.x < 2 * kWave) (&s_begin[0][0])[threadIdx.x] = 0ull;
+    base[threadIdx.x] = tstart + tcol;
 
     // this thread's items: slot range (the exclusive scan of the items'
     // pairs in the band, in item order), tile rectangle clipped to the band,
     // index
-    const int sel = ws.hdr->item_sel & 1;
     // (counts and tile coordinates in the band fit 16 bits)
     uint32_t i_off[kMyItems], i_gi[kMyItems];
     uint32_t i_cy[kMyItems];  // pair count | first tile row of the band << 16
     uint32_t i_x[kMyItems];   // first | last tile column << 16
 #pragma unroll
     for (int k = 0; k < kMyItems; ++k) {
-        const int64_t j = b.j0 + (int64_t)threadIdx.x * kMyItems + k;
         i_cy[k] = 0;
-        i_off[k] = 0;
-        i_gi[k] = 0;
         i_x[k] = 0;
-        if (j < b.j1) {
-            const uint32_t cnt = ws.icounts[j];
-            if (cnt > 0) {
-                const uint64_t val = ws.ivals[sel][j];
-                i_gi[k] = (uint32_t)val - (uint32_t)b.view * (uint32_t)ws.n;
-                const TileRect r = item_tile_rect(ws, val, tile);
-                const int y0 = max(r.ty0, bd.y0), y1 = min(r.ty1, bd.y1);
-                i_x[k] = (uint32_t)r.tx0 | ((uint32_t)r.tx1 << 16);
-                if (y0 <= y1)
-                    i_cy[k] = (uint32_t)((r.tx1 - r.tx0 + 1) * (y1 - y0 + 1)) | ((uint32_t)(y0 - bd.y0) << 16);
-            }
+        i_gi[k] = (uint32_t)ival[k] - (uint32_t)b.view * (uint32_t)ws.n;
+        if (icnt[k] > 0) {
+            const TileRect r = item_tile_rect(ws, ival[k], tile);
+            const int y0 = max(r.ty0, bd.y0), y1 = min(r.ty1, bd.y1);
+            i_x[k] = (uint32_t)r.tx0 | ((uint32_t)r.tx1 << 16);
+            if (y0 <= y1)
+                i_cy[k] = (uint32_t)((r.tx1 - r.tx0 + 1) * (y1 - y0 + 1)) | ((uint32_t)(y0 - bd.y0) << 16);
         }
     }
     // a thread's items are consecutive (j0 + thread kMyItems + k): one block
-    // scan of the thread sums, of the band's pairs and, for the first band's
-    // workgroup, of the items' whole counts (the offsets, from the
-    // partition's first pair)
-    uint32_t E;
+    // scan of the thread sums, of the band's pairs, of the items that have any
+    // and, for the first band's workgroup, of the items' whole counts (the
+    // offsets, from the partition's first pair)
+    uint32_t E, ord;
     {
-        __shared__ alignas(16) uint32_t s_scan[2 * kScanLds];
-        uint32_t sums[2] = {0, 0}, tot[2];
-#pragma unroll
-        for (int k = 0; k < kMyItems; ++k) sums[0] += i_cy[k] & 0xffffu;
-        uint32_t whole[kMyItems];
+        __shared__ alignas(16) uint32_t s_scan[3 * kScanLds];
+        uint32_t sums[3] = {0, 0, 0}, tot[3];
 #pragma unroll
         for (int k = 0; k < kMyItems; ++k) {
-            const int64_t j = b.j0 + (int64_t)threadIdx.x * kMyItems + k;
-            whole[k] = bands > 1 && bd.y0 == 0 && j < b.j1 ? ws.icounts[j] : i_cy[k] & 0xffffu;
-            sums[1] += whole[k];
+            const uint32_t cnt = i_cy[k] & 0xffffu;
+            sums[0] += cnt;
+            sums[1] += cnt != 0;
+            sums[2] += icnt[k];
         }
-        block_excl_scans<2>(sums, s_scan, tot);
+        block_excl_scans<3>(sums, s_scan, tot);
         E = tot[0];
-        uint32_t run = sums[0], off = ws.bin_pstart[part] + sums[1];
+        uint32_t run = sums[0], off = pstart + sums[2], o = sums[1];
+        ord = o;
 #pragma unroll
         for (int k = 0; k < kMyItems; ++k) {
-            i_off[k] = run;
-            run += i_cy[k] & 0xffffu;
-            const int64_t j = b.j0 + (int64_t)threadIdx.x * kMyItems + k;
-            if (bd.y0 == 0 && j < b.j1) ws.offsets[j] = off;
-            off += whole[k];
+            const uint32_t cnt = i_cy[k] & 0xffffu;
+            i_off[k] = cnt ? run : ~0u;   // (none: past every window)
+            if (cnt) {
+                const uint32_t tx0 = i_x[k] & 0xffffu, cols = (i_x[k] >> 16) - tx0 + 1u;
+                s_item[o++] = (uint64_t)(((i_cy[k] >> 16) * (uint32_t)b.tiles_x + tx0) | (cols << 16)) | ((uint64_t)run << 32);
+            }
+            run += cnt;
+            if (bd.y0 == 0 && j0 + k < b.j1) ws.offsets[j0 + k] = off;
+            off += icnt[k];
         }
     }
 
-    const int w = threadIdx.x / kWave;
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     const int lane = lane_id();
-    const uint64_t lt_mask = (1ull << lane) - 1ull;
     const int gb = ws.pair_gbits;
     uint32_t *out_t = ws.ptile[ws.pair_sel];
     uint32_t *out_v = ws.pval[ws.pair_sel];
 
-    for (uint32_t w0 = 0; w0 < E; w0 += kBinWindow) {
+    uint32_t first = 0;   // items begun before the window
+    int buf = 0;
+    for (uint32_t w0 = 0; w0 < E; w0 += kBinWindow, buf ^= 1) {
         const uint32_t w1 = min(E, w0 + (uint32_t)kBinWindow);
         const int wn = (int)(w1 - w0);
-        for (int k = threadIdx.x; k < NW * (LT / 2); k += NT) (&h16[0][0])[k] = 0u;
+        for (int k = threadIdx.x; k < NW * (LT / 2) / 4; k += NT)
+            reinterpret_cast<uint4 *>(&h16[0][0])[k] = make_uint4(0u, 0u, 0u, 0u);
         if (threadIdx.x == 0) s_alloc = 0u;
-        // emission: each item writes its pairs inside the window, row-major
-        // over its rectangle
+        uint32_t o = ord;
 #pragma unroll
         for (int k = 0; k < kMyItems; ++k) {
-            const uint32_t cnt = i_cy[k] & 0xffffu;
-            const uint32_t a = max(i_off[k], w0), e = min(i_off[k] + cnt, w1);
-            if (cnt == 0 || a >= e) continue;
-            const uint32_t tx0 = i_x[k] & 0xffffu, rw = (i_x[k] >> 16) - tx0 + 1u;
-            uint32_t lt = (i_cy[k] >> 16) * (uint32_t)b.tiles_x + tx0;
-            uint32_t left = rw;   // pairs left in the row
-            // (only an item begun in an earlier window skips whole rows)
-            uint32_t skip = a - i_off[k];
-            for (; skip >= rw; skip -= rw) lt += (uint32_t)b.tiles_x;
-            lt += skip;
-            left -= skip;
-            const uint32_t step = (uint32_t)b.tiles_x - rw;   // from a row's end to the next row
-#pragma unroll 1
-            for (uint32_t s = a - w0; s < e - w0; ++s) {
-                s_lt[s] = (uint16_t)lt++;
-                s_gi[s] = i_gi[k];
-                if (--left == 0) {
-                    left = rw;
-                    lt += step;
-                }
-            }
+            if (i_off[k] != ~0u) s_igi[o++] = i_gi[k];
+            const uint32_t a = i_off[k] - w0;   // (wraps if begun before the window)
+            if (a < (uint32_t)wn)
+                atomicOr(reinterpret_cast<unsigned long long *>(&s_begin[buf][a / kWave]), 1ull << (a % kWave));
         }
         __syncthreads();
+        // emission, a lane for each slot: the items begun up to the slot are
+        // counted, which numbers the slot's item, and the slot's place in the
+        // item's rectangle (row-major) gives the tile.  Every lane has the same
+        // work whatever the items' sizes; where a thread wrote its items' pairs
+        // one by one, a wavefront took as long as its largest
+        const uint64_t begin = s_begin[buf][lane];
+        if (threadIdx.x < kWave) s_begin[buf ^ 1][threadIdx.x] = 0ull;
+        s_tab[lane] = 0ull;
+        const uint32_t begun = wave_incl_scan((uint32_t)__popcll(begin));
+        uint32_t tt[kRows], gi[kRows];
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+            const int row = w * kRows + r;
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)begin, row);
+            const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(begin >> 32), row);
+            const uint64_t m = (uint64_t)lo | ((uint64_t)hi << 32);
+            // the last item begun before the row's second slot, then one for
+            // every beginning from there up to the lane's slot
+            const uint32_t id0 = first + (uint32_t)__builtin_amdgcn_readlane((int)begun, row) - (uint32_t)__popcll(m >> 1) - 1u;
+            const uint32_t id = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 33), __builtin_amdgcn_mbcnt_lo((uint32_t)(m >> 1), id0));
+            const uint64_t it = s_item[id];
+            const uint32_t tc = (uint32_t)it;
+            gi[r] = s_igi[id];
+            const uint32_t cols = tc >> 16;
+            const uint32_t k = w0 + (uint32_t)(row * kWave + lane) - (uint32_t)(it >> 32);
+            // k / cols, both at most 1024 (LT): with half a unit added to k the
+            // quotient is at least 0.5 / 1024 of itself from a whole number
+            const uint32_t y = (uint32_t)(((float)k + 0.5f) * __builtin_amdgcn_rcpf((float)cols));
+            tt[r] = (tc & 0xffffu) + k + __umul24(y, (uint32_t)b.tiles_x - cols);
+        }
+        first += (uint32_t)__builtin_amdgcn_readlane((int)begun, kWave - 1);
         // ranking: wavefront w owns slots [w kRows 64, (w + 1) kRows 64)
         uint32_t rt[kRows];   // rank in the wavefront | tile << 16 (both below 2^16)
 #pragma unroll
         for (int r = 0; r < kRows; ++r) {
             const int slot = (w * kRows + r) * kWave + lane;
             const bool valid = slot < wn;
-            const uint32_t t = valid ? s_lt[slot] : 0u;
+            const uint32_t t = valid ? tt[r] : 0u;
             // lanes of the row with this tile: the lanes whose low kHashBits
             // agree (one bit each, OR-ed into this wavefront's table slot,
             // read back, then cleared; a wavefront's LDS operations complete
             // in order) that also agree in the high bits (one ballot each)
-            uint64_t *slotp = &s_tab[w][t & (kHash - 1)];
+            uint64_t *slotp = &s_tab[t & (kHash - 1)];
             if (valid) atomicOr(reinterpret_cast<unsigned long long *>(slotp), 1ull << lane);
             const uint64_t same_low = *slotp;
             *slotp = 0ull;
@@ -441,7 +486,7 @@ __global__ __launch_bounds__(1024, 8) void k_bin_scatter(Ws ws, const xg_camera 
             // every lane reads its tile's count, then the first lane of each
             // tile adds the row's (two tiles share a word: an atomic, whose
             // result nothing waits for)
-            const uint32_t below = (uint32_t)__popcll(peers & lt_mask);
+            const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0u));
             const uint32_t sh = 16u * (t & 1u);
             const uint32_t old = (h16[w][t >> 1] >> sh) & 0xffffu;
             if (valid && below == 0) atomicAdd(&h16[w][t >> 1], (uint32_t)__popcll(peers) << sh);
@@ -453,7 +498,7 @@ __global__ __launch_bounds__(1024, 8) void k_bin_scatter(Ws ws, const xg_camera 
         // totals and one allocation per wavefront (blocks in any order, each
         // tile's block contiguous)
         constexpr int kPairsPerThread = (LT / 2 + NT - 1) / NT;
-        uint32_t adv[kPairsPerThread];
+        uint32_t adv[kPairsPerThread], pos[kPairsPerThread];
 #pragma unroll
         for (int k = 0; k < kPairsPerThread; ++k) {
             const int tw = k * NT + threadIdx.x;
@@ -475,7 +520,13 @@ __global__ __launch_bounds__(1024, 8) void k_bin_scatter(Ws ws, const xg_camera 
             if (lane == 0 && wsum) wbase = atomicAdd(&s_alloc, wsum);
             wbase = (uint32_t)__builtin_amdgcn_readfirstlane((int)wbase);
             const uint32_t st = wbase + incl - tot;
-            if (tw < LT / 2 && tot) s_lst[tw] = st | ((st + lo) << 16);
+            pos[k] = st;
+            if (tw < LT / 2 && tot) {
+                s_lst[tw] = st | ((st + lo) << 16);
+                // for the placement: the list entry of window position 0
+                base[2 * tw] -= st;
+                base[2 * tw + 1] -= st + lo;
+            }
         }
         __syncthreads();
         // each slot's window position: its tile's block, the wavefronts
@@ -488,7 +539,9 @@ __global__ __launch_bounds__(1024, 8) void k_bin_scatter(Ws ws, const xg_camera 
                 const uint32_t sh = 16u * (t & 1u);
                 const uint32_t off = (h16[w][t >> 1] >> sh) & 0xffffu;
                 const uint32_t st = (s_lst[t >> 1] >> sh) & 0xffffu;
-                s_perm[st + off + (rt[r] & 0xffffu)] = (uint16_t)slot;
+                const uint32_t k = st + off + (rt[r] & 0xffffu);
+                s_lt[k] = (uint16_t)t;
+                s_gi[k] = gi[r];
             }
         }
         __syncthreads();
@@ -498,11 +551,9 @@ __global__ __launch_bounds__(1024, 8) void k_bin_scatter(Ws ws, const xg_camera 
         for (int r = 0; r < kRows; ++r) {
             const int k = (w * kRows + r) * kWave + lane;
             if (k < wn) {
-                const int slot = s_perm[k];
-                const uint32_t t = s_lt[slot];
-                const uint32_t gi = s_gi[slot];
-                const uint32_t st = (s_lst[t >> 1] >> (16u * (t & 1u))) & 0xffffu;
-                const uint32_t dst = base[t] + ((uint32_t)k - st);
+                const uint32_t t = s_lt[k];
+                const uint32_t gi = s_gi[k];
+                const uint32_t dst = base[t] + (uint32_t)k;
                 const uint32_t gt = (uint32_t)(b.toff + bd.first) + t;
                 if (dst >= (uint64_t)ws.cap) continue;   // never: the counts add up to the slots
                 if (gb) {
@@ -517,9 +568,10 @@ __global__ __launch_bounds__(1024, 8) void k_bin_scatter(Ws ws, const xg_camera 
 #pragma unroll
         for (int k = 0; k < kPairsPerThread; ++k) {
             const int tw = k * NT + threadIdx.x;
-            if (tw < LT / 2) {
-                if (2 * tw < bd.tiles) base[2 * tw] += adv[k] & 0xffffu;
-                if (2 * tw + 1 < bd.tiles) base[2 * tw + 1] += adv[k] >> 16;
+            if (tw < LT / 2 && adv[k]) {   // past the window's pairs
+                const uint32_t lo = adv[k] & 0xffffu;
+                base[2 * tw] += pos[k] + lo;
+                base[2 * tw + 1] += pos[k] + lo + (adv[k] >> 16);
             }
         }
         // the next window's counters are cleared before its ranking, after

@@ -207,19 +207,18 @@ __device__ __forceinline__ TileRect item_tile_rect(const Ws &ws, uint64_t val, i
 
 // Lanes of the wavefront whose BITS-bit key equals this lane's (one ballot
 // per key bit), restricted to `valid` lanes.
-// Per bit: one ballot (a wavefront-uniform mask) and, per half of the
-// mask, one XOR with the lane's all-ones-if-clear word and one AND.
+// Per bit: the bit spread over a word, one compare (a wavefront-uniform mask)
+// and, per half of the mask, one three-operand instruction.
 template <int BITS>
 __device__ __forceinline__ uint64_t match_peers(uint32_t d, bool valid) {
     const uint64_t v = __ballot(valid);
     uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
 #pragma unroll
     for (int b = 0; b < BITS; ++b) {
-        const uint32_t bit = (d >> b) & 1u;
-        const uint64_t bal = __ballot(bit);
-        const uint32_t inv = bit - 1u;   // 0 when the bit is set, all ones when clear
-        lo &= (uint32_t)bal ^ inv;
-        hi &= (uint32_t)(bal >> 32) ^ inv;
+        const int bit = (int)(d << (31 - b)) >> 31;   // all ones when the bit is set
+        const uint64_t bal = __ballot(bit < 0);
+        lo &= ~((uint32_t)bal ^ (uint32_t)bit);
+        hi &= ~((uint32_t)(bal >> 32) ^ (uint32_t)bit);
     }
     return (uint64_t)lo | ((uint64_t)hi << 32);
 }
