@@ -128,8 +128,7 @@ class Frame:
             self._allocate()
 
     def ws_tensor(self, offset: int, dtype: torch.dtype, count: int) -> torch.Tensor:
-        itemsize = torch.empty((), dtype=dtype).element_size()
-        return self.ws[offset:offset + count * itemsize].view(dtype)
+        return self.ws[offset:offset + count * dtype.itemsize].view(dtype)
 
     def status(self) -> int:
         return int(self.ws_tensor(self.layout.status, torch.int32, 1).item())
@@ -140,6 +139,21 @@ class Frame:
 
     def n_pairs(self) -> int:
         return int(self.ws_tensor(self.layout.n_pairs, torch.int32, 1).item())
+
+    def _status_pairs(self, then=None) -> tuple[int, int]:
+        """status() and n_pairs() in one read; ``then`` is called (to enqueue
+        more work) between its start and the wait for it."""
+        first = min(self.layout.status, self.layout.n_pairs)
+        i, j = (self.layout.status - first) // 4, (self.layout.n_pairs - first) // 4
+        words = torch.empty(max(i, j) + 1, dtype=torch.int32, pin_memory=True)
+        words.copy_(self.ws_tensor(first, torch.int32, words.numel()), non_blocking=True)
+        read = torch.cuda.Event()
+        read.record(torch.cuda.current_stream(self.device))
+        if then is not None:
+            then()
+        read.synchronize()
+        words = words.tolist()
+        return words[i], words[j]
 
     def sorted_pairs(self, stream=None):
         """(keys, values, ranges) of the sorted lists, for inspection
@@ -174,14 +188,21 @@ class Frame:
     def fit_capacity(self, g: dict, headroom: float = 1.25) -> int:
         """Runs preprocess + sort, grows the workspace if the pairs did not fit
         (synchronises).  Returns the pair count."""
-        self.preprocess_sort(g)
-        p = self.n_pairs()
-        if self.status() == X.XG_ECAPACITY or p > self.capacity:
-            self.set_capacity(int(math.ceil(p * headroom)) + 1024)
+        return self._fit(g, headroom, None)
+
+    def _fit(self, g: dict, headroom: float, out) -> int:
+        """fit_capacity(), with a render of the lists into ``out`` (unless
+        None) enqueued before the host waits for the status, so that the device
+        has work when the host goes on (the blend of a failed list build reads
+        empty lists)."""
+        for last in (False, True):
             self.preprocess_sort(g)
-            p = self.n_pairs()
-        if self.status() != X.XG_OK:
-            raise X.XgError(self.status(), "fit_capacity")
+            status, p = self._status_pairs(None if out is None else lambda: self.render_fwd(g, out))
+            if last or not (status == X.XG_ECAPACITY or p > self.capacity):
+                break
+            self.set_capacity(int(math.ceil(p * headroom)) + 1024)
+        if status != X.XG_OK:
+            raise X.XgError(status, "fit_capacity")
         return p
 
     def new_outputs(self):
@@ -333,13 +354,14 @@ class DRRFunction(torch.autograd.Function):
         g = {"means": means.detach().contiguous(), "scales": scales.detach().contiguous(),
              "quats": quats.detach().contiguous(), "opacity": opacity.detach().contiguous(),
              "intensity": intensity.detach().contiguous()}
-        frame.fit_capacity(g)          # preprocess + lists; grows the workspace on overflow
-        image, final_t, n_contrib = frame.render_fwd(g)
+        image, final_t, n_contrib = out = frame.new_outputs()
+        frame._fit(g, 1.25, out)       # preprocess, lists, blend; again in a larger workspace on overflow
         ctx.frame = frame
         ctx.generation = frame.generation
         ctx.save_for_backward(g["means"], g["scales"], g["quats"], g["opacity"], g["intensity"],
                               final_t, n_contrib)
         ctx.mark_non_differentiable(final_t, n_contrib)
+        ctx.set_materialize_grads(False)   # no zeros for the two outputs without a gradient
         return image, final_t, n_contrib
 
     @staticmethod
@@ -351,7 +373,8 @@ class DRRFunction(torch.autograd.Function):
         means, scales, quats, opacity, intensity, final_t, n_contrib = ctx.saved_tensors
         g = {"means": means, "scales": scales, "quats": quats, "opacity": opacity,
              "intensity": intensity}
-        grads = frame.backward(g, dl_dimage.contiguous(), final_t, n_contrib)
+        dl_dimage = torch.zeros_like(final_t) if dl_dimage is None else dl_dimage.contiguous()
+        grads = frame.backward(g, dl_dimage, final_t, n_contrib)
         return (grads["means"], grads["scales"], grads["quats"], grads["opacity"],
                 grads["intensity"], None)
 
