@@ -75,7 +75,7 @@ struct Plan {
     size_t icounts, scan_tmp, ikeys[2], ivals[2], ptile[2], pval[2], ghist, vhist, vctr, bin_cnt, bin_csum, bin_ptot,
         bin_pstart, lookback[2], tile_order, xcd_order, blend_order, ssim, entry_mask;
     int64_t total_px, total_tiles, n_items;
-    int32_t item_blocks, pair_blocks, tile_bits, pair_passes, pair_gbits, bin_tiles, bin_bands, bin_ppv, bin_items;
+    int32_t item_blocks, item_per, pair_blocks, tile_bits, pair_passes, pair_gbits, bin_tiles, bin_bands, bin_ppv, bin_items;
     ViewSort view_sort;
     bool sort_fold;
 };
@@ -89,7 +89,13 @@ xg_status make_plan(const xg_frame *f, bool need_ws, Plan &P) {
     const int64_t cap = f->pair_capacity;
     P.n_items = ni;
     // the items are sorted within each view: every view starts a partition
-    P.item_blocks = (int32_t)((int64_t)f->n_views * (((int64_t)f->n + kItemSortBlock - 1) / kItemSortBlock));
+    // (the sizes: at kItemSortItems)
+    for (P.item_per = 2;; P.item_per *= 2) {
+        const int64_t block = (int64_t)kItemSortThreads * P.item_per, per_view = ((int64_t)f->n + block - 1) / block;
+        const int64_t blocks = (int64_t)f->n_views * per_view;
+        P.item_blocks = (int32_t)blocks;
+        if (P.item_per == kItemSortItems || (blocks <= kItemSortMost && per_view <= kItemSortChain * P.item_per)) break;
+    }
     // Tile lists by counting, in rows of at most kBinMaxTilesX tiles, when
     // every view has at most 4096 tiles, or more but not many ranking
     // workgroups (partitions x bands): each of those reads its partition
@@ -246,6 +252,7 @@ Ws resolve(const xg_frame *f, const Plan &P) {
     w.n_views = f->n_views;
     w.tile_bits = P.tile_bits;
     w.item_blocks = P.item_blocks;
+    w.item_per = P.item_per;
     w.pair_blocks = P.pair_blocks;
     w.pair_passes = P.pair_passes;
     w.pair_sel = P.pair_passes & 1;

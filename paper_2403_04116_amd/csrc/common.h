@@ -135,6 +135,7 @@ struct Ws {
     int32_t n_views;
     int32_t tile_bits;     // bits of the largest global tile id
     int32_t item_blocks;   // radix-sort blocks over the items
+    int32_t item_per;      // their items per thread (2, 4 or 8)
     int32_t pair_blocks;   // radix-sort blocks over the pair capacity
     int32_t pair_passes;   // 8-bit passes over the tile id
     int32_t pair_sel;      // buffer holding the tile-sorted pairs (pair_passes & 1)
@@ -241,10 +242,20 @@ constexpr int kScanItems = 8;
 constexpr int kScanBlock = kScanThreads * kScanItems;   // 2048 elements
 
 // Radix-sort partitions (keys per workgroup = threads x keys per thread);
-// larger partitions shorten the look-back chains, these sizes measured best.
-constexpr int kItemSortThreads = 1024, kItemSortItems = 8;    // 8192 items
+// larger partitions shorten the look-back chains, smaller ones the chain of
+// phases inside a workgroup.  The items' hold 8192, 4096 or 2048: the smallest
+// that make no more partitions than the device has CUs (a workgroup of 8192 fills a
+// CU's LDS) and no longer chains in a view than 128 of 4096 or 64 of 2048.
+// Forward passes with 8192 / 4096 / 2048: one view of 43k items 108 / 95 / 89 us;
+// one of 400k 147.6 / 143.9 / 149.7, of 1M (245 partitions of 4096) 185 / 188 /
+// 208; 8 views of 50k 155 / 147 / 145; 4 of 200k 212 / 207 / 217; 8 of 200k (392
+// of 4096), a training step, 452 / 472 / 482.  1024: 43k 88.5, 10k 82.7
+// against 83.7, but 8 views of 50k 155.
+constexpr int kItemSortThreads = 1024;
+constexpr int kItemSortItems = 8;        // most items per thread
+constexpr int kItemSortMost = 256;       // most partitions of the smaller sizes
+constexpr int kItemSortChain = 32;       // and of a view, times the items per thread
 constexpr int kPairSortThreads = 1024, kPairSortItems = 16;   // 16384 pairs
-constexpr int kItemSortBlock = kItemSortThreads * kItemSortItems;
 constexpr int kPairSortBlock = kPairSortThreads * kPairSortItems;
 // packed pairs move 4-byte keys only, so a partition holds more of them
 constexpr int kPackedSortThreads = 1024, kPackedSortItems = 16;

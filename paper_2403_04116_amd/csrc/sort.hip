@@ -17,7 +17,7 @@
 //
 // Each sort is one histogram launch (the digit counts of every pass in one
 // read of the keys) and one launch per 8-bit pass, in the single-pass
-// ("onesweep") form: a workgroup takes the next partition (8192 items or
+// ("onesweep") form: a workgroup takes the next partition (2048 to 8192 items or
 // 16384 pairs) from an atomic counter, ranks its keys stably (rows of 64
 // keys matched by digit through a per-wavefront LDS table of lane masks,
 // or by ballots), publishes its per-digit counts, stages its keys
@@ -44,7 +44,8 @@ struct Ctl {
 };
 
 // Float32 depth bits of the items (0xffffffff for culled items, which the
-// digit clamps to the largest kept depth).
+// digit clamps to the largest kept depth).  ITEMS: per thread.
+template <int ITEMS>
 struct ItemSort {
     using Key = uint32_t;
     using Val = uint64_t;   // item index | packed tile rectangle << 32
@@ -71,7 +72,7 @@ struct ItemSort {
         return ws.counts[(uint32_t)v];
     }
     static __device__ __forceinline__ int blocks(const Ws &ws) { return ws.item_blocks; }
-    static constexpr int kThreads = kItemSortThreads, kItems = kItemSortItems;
+    static constexpr int kThreads = kItemSortThreads, kItems = ITEMS;
     static constexpr bool kHasVal = true;
     static constexpr bool kTabRank = true;   // LDS lane-mask table for the ranking (see k_onesweep)
     // sorted within each view: the items of view v stay in [v n, (v + 1) n)
@@ -679,7 +680,7 @@ __global__ __launch_bounds__(kViewSortThreads) void k_sort_view(Ws ws, const xg_
         __syncthreads();
         uint32_t d[ITEMS];
 #pragma unroll
-        for (int r = 0; r < ITEMS; ++r) d[r] = ItemSort::digit(key[r], c, shift);
+        for (int r = 0; r < ITEMS; ++r) d[r] = ItemSort<ITEMS>::digit(key[r], c, shift);
         rank_rows<ITEMS>(d, valid, rows, stab + w * kRadix, whist + w * kRadix, rank);
         __syncthreads();
         uint32_t acc = 0;
@@ -726,7 +727,7 @@ __global__ __launch_bounds__(kViewSortThreads) void k_sort_view(Ws ws, const xg_
         const int e = elem(r);
         cnt[r] = 0;
         if (e < n) {
-            cnt[r] = ItemSort::count_of(ws, val[r]);
+            cnt[r] = ItemSort<ITEMS>::count_of(ws, val[r]);
             ws.ivals[1][vbase + e] = val[r];
             ws.icounts[vbase + e] = cnt[r];
         }
@@ -931,10 +932,15 @@ template <class S>
 hipError_t radix_passes(const Ws &ws, int passes, int blocks, hipStream_t s,
                         const uint32_t *depth_part = nullptr, int64_t nparts = 0) {
     const unsigned nb = (unsigned)(blocks > 0 ? blocks : 1);
-    if (S::kSegmented && ws.sort_fold) {
-        hipLaunchKernelGGL((k_sort_hist<ItemSort, true>), dim3(nb), dim3(ItemSort::kThreads), 0, s, ws, passes,
-                           depth_part, nparts);
-    } else {
+    bool folded = false;
+    if constexpr (S::kSegmented) {
+        if (ws.sort_fold) {
+            hipLaunchKernelGGL((k_sort_hist<S, true>), dim3(nb), dim3(S::kThreads), 0, s, ws, passes, depth_part,
+                               nparts);
+            folded = true;
+        }
+    }
+    if (!folded) {
         unsigned np = (unsigned)(((int64_t)blocks * kRadix + 255) / 256);
         if (np > 2048) np = 2048;
         hipLaunchKernelGGL(k_sort_prep<S>, dim3(np > 0 ? np : 1), dim3(256), 0, s, ws, depth_part, nparts);
@@ -976,7 +982,12 @@ hipError_t launch_sort_items(const Ws &ws, const xg_camera *cams, const Params &
     // bits, passes past the varying bits return at once
     const int passes = (32 + kRadixBits - 1) / kRadixBits;
     if (passes > kMaxPasses) return hipErrorInvalidValue;
-    return radix_passes<ItemSort>(ws, passes, ws.item_blocks, s, ws.scan_tmp, nparts);
+    switch (ws.item_per) {
+        case 2: return radix_passes<ItemSort<2>>(ws, passes, ws.item_blocks, s, ws.scan_tmp, nparts);
+        case 4: return radix_passes<ItemSort<4>>(ws, passes, ws.item_blocks, s, ws.scan_tmp, nparts);
+        case kItemSortItems: return radix_passes<ItemSort<kItemSortItems>>(ws, passes, ws.item_blocks, s, ws.scan_tmp, nparts);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 
