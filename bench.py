@@ -763,7 +763,7 @@ def main():
                                    "(Gaussian, wavefront) reduction",
                      "note": "the model prices each reduction as a 6-level butterfly per value "
                              f"({WAVE_INSTR_REDUCTION} wavefront instructions); the backward's "
-                             "reduce-scatter issues about 18 per entry, so the model's lane "
+                             "reduce-scatter issues about 13 per entry, so the model's lane "
                              "operations exceed the instructions issued and frac can pass 1"},
         "cpu_baseline": cpu,
         "graph": graph,

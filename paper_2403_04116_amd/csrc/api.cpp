@@ -129,9 +129,10 @@ xg_status make_plan(const xg_frame *f, bool need_ws, Plan &P) {
            f->n_views * (((int64_t)f->n + P.bin_items / 2 - 1) / (P.bin_items / 2)) * P.bin_bands <= kBinResident)
         P.bin_items /= 2;
     // A view of at most 8192 items is sorted by one workgroup in LDS instead
-    // of the radix passes' six launches (8000 items, one view: 20 us less; 400
-    // views: 36 us less; at 16 000 the one CU's LDS takes as long as the
-    // launches); and where a view has at most 4096, the frame is small (every
+    // of the radix passes' launches (whole forward pass, 5000 items in one view
+    // 64 us against 75 with partitions of 2048, 8000 in one view 74 against 79,
+    // in 100 views 191 against 206; at 16 000 the one CU's LDS takes as long as
+    // the launches); and where a view has at most 4096, the frame is small (every
     // workgroup adds up all views' counts) and the counts fit that
     // workgroup's LDS, the tile lists are counted there too instead of in
     // three launches more (8000 items: 18 us slower than those).
