@@ -143,6 +143,8 @@ class Frame:
     def _status_pairs(self, then=None) -> tuple[int, int]:
         """status() and n_pairs() in one read; ``then`` is called (to enqueue
         more work) between its start and the wait for it."""
+        if torch.cuda.is_current_stream_capturing():
+            raise RuntimeError("the status word cannot be waited for while the stream is being captured")
         first = min(self.layout.status, self.layout.n_pairs)
         i, j = (self.layout.status - first) // 4, (self.layout.n_pairs - first) // 4
         words = torch.empty(max(i, j) + 1, dtype=torch.int32, pin_memory=True)
