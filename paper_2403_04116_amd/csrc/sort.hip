@@ -71,7 +71,6 @@ struct ItemSort {
             return (uint32_t)((t.tx1 - t.tx0 + 1) * (t.ty1 - t.ty0 + 1));
         return ws.counts[(uint32_t)v];
     }
-    static __device__ __forceinline__ int blocks(const Ws &ws) { return ws.item_blocks; }
     static constexpr int kThreads = kItemSortThreads, kItems = ITEMS;
     static constexpr bool kHasVal = true;
     static constexpr bool kTabRank = true;   // LDS lane-mask table for the ranking (see k_onesweep)
@@ -114,7 +113,6 @@ struct PairSort {
     static __device__ __forceinline__ Key *keys(const Ws &ws, int b) { return ws.ptile[b]; }
     static __device__ __forceinline__ Val *vals(const Ws &ws, int b) { return ws.pval[b]; }
     static __device__ __forceinline__ uint32_t count_of(const Ws &, Val) { return 0; }
-    static __device__ __forceinline__ int blocks(const Ws &ws) { return ws.pair_blocks; }
     static constexpr int kThreads = kPairSortThreads, kItems = kPairSortItems;
     static constexpr bool kHasVal = true;
     static constexpr bool kTabRank = false;  // its keys and values fill the LDS
@@ -144,7 +142,6 @@ struct PackedPairSort {
     static __device__ __forceinline__ Key *keys(const Ws &ws, int b) { return ws.ptile[b]; }
     static __device__ __forceinline__ Val *vals(const Ws &, int) { return nullptr; }
     static __device__ __forceinline__ uint32_t count_of(const Ws &, Val) { return 0; }
-    static __device__ __forceinline__ int blocks(const Ws &ws) { return ws.pair_blocks; }
     static constexpr int kThreads = kPackedSortThreads, kItems = kPackedSortItems;
     static constexpr bool kHasVal = false;
     static constexpr bool kTabRank = true;
@@ -952,8 +949,6 @@ hipError_t radix_passes(const Ws &ws, int passes, int blocks, hipStream_t s,
         hipLaunchKernelGGL(k_onesweep<S>, dim3(nb), dim3(S::kThreads), 0, s, ws, p, passes);
     return hipGetLastError();
 }
-
-unsigned grid256(int64_t n) { return (unsigned)((n + 255) / 256 > 0 ? (n + 255) / 256 : 1); }
 
 }  // namespace
 
