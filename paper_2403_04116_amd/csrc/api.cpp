@@ -72,7 +72,7 @@ xg_status check_frame(const xg_frame *f, bool need_ws, int64_t *tot_px, int64_t 
 
 struct Plan {
     xg_ws_layout lay;
-    size_t icounts, scan_tmp, ikeys[2], ivals[2], ptile[2], pval[2], ghist, vhist, vctr, bin_cnt, bin_csum, bin_ptot,
+    size_t icounts, scan_tmp, depth_part, ikeys[2], ivals[2], ptile[2], pval[2], ghist, vhist, vctr, bin_cnt, bin_csum, bin_ptot,
         bin_pstart, lookback[2], tile_order, xcd_order, blend_order, ssim, entry_mask;
     int64_t total_px, total_tiles, n_items;
     int32_t item_blocks, item_per, pair_blocks, tile_bits, pair_passes, pair_gbits, bin_tiles, bin_bands, bin_ppv, bin_items;
@@ -163,8 +163,7 @@ xg_status make_plan(const xg_frame *f, bool need_ws, Plan &P) {
     P.pair_blocks = (int32_t)((cap + pblock - 1) / pblock);
     const int64_t lb_words = (int64_t)kRadix * (P.item_blocks > P.pair_blocks ? P.item_blocks : P.pair_blocks);
     const int64_t scan_words = (ni + kScanBlock - 1) / kScanBlock + 1;
-    // depth partials: one pair per preprocess workgroup
-    const int64_t part_words = 2 * ((ni + kPreThreads - 1) / kPreThreads) + 2;
+    const int64_t part_words = 2 * ((ni + kPreThreads - 1) / kPreThreads);
     size_t o = 0;
     xg_ws_layout &L = P.lay;
     memset(&L, 0, sizeof(L));
@@ -176,7 +175,8 @@ xg_status make_plan(const xg_frame *f, bool need_ws, Plan &P) {
     L.counts = o;             o = align_up(o + 4 * (size_t)ni);
     P.icounts = o;            o = align_up(o + 4 * (size_t)ni);
     L.offsets = o;            o = align_up(o + 4 * (size_t)ni);
-    P.scan_tmp = o;           o = align_up(o + 4 * (size_t)(scan_words > part_words ? scan_words : part_words));
+    P.scan_tmp = o;           o = align_up(o + 4 * (size_t)scan_words);
+    P.depth_part = o;         o = align_up(o + 4 * (size_t)part_words);
     for (int b = 0; b < 2; ++b) { P.ikeys[b] = o; o = align_up(o + 4 * (size_t)ni); }
     for (int b = 0; b < 2; ++b) { P.ivals[b] = o; o = align_up(o + 8 * (size_t)ni); }
     for (int b = 0; b < 2; ++b) { P.ptile[b] = o; o = align_up(o + 4 * (size_t)cap); }
@@ -216,6 +216,7 @@ Ws resolve(const xg_frame *f, const Plan &P) {
     w.icounts = (uint32_t *)(b + P.icounts);
     w.offsets = (uint32_t *)(b + P.lay.offsets);
     w.scan_tmp = (uint32_t *)(b + P.scan_tmp);
+    w.depth_part = (uint32_t *)(b + P.depth_part);
     for (int k = 0; k < 2; ++k) {
         w.ikeys[k] = (uint32_t *)(b + P.ikeys[k]);
         w.ivals[k] = (uint64_t *)(b + P.ivals[k]);

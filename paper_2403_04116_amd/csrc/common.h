@@ -103,6 +103,8 @@ struct Ws {
     uint32_t *icounts;     // the same counts in depth-sorted item order
     uint32_t *offsets;     // exclusive scan of icounts
     uint32_t *scan_tmp;
+    uint32_t *depth_part;  // (min, max) depth bits of each preprocess workgroup's kept items: kept until the
+                           // next preprocess, every list build reads them
     uint32_t *ikeys[2];    // item sort keys (float32 depth bits; 0xffffffff when culled)
     uint64_t *ivals[2];    // item sort values: (view, Gaussian) index | tile rectangle << 32
     uint32_t *ptile[2];    // pair sort keys (global tile id)

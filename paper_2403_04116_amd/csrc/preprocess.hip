@@ -641,10 +641,9 @@ hipError_t launch_preprocess(const Ws &ws, const xg_gaussians &g, const xg_camer
                              const Params &p, bool colours, hipStream_t s) {
     const int64_t nb = (ws.n_items + kPreThreads - 1) / kPreThreads;
     if (nb > 0x7fffffff) return hipErrorInvalidValue;
-    // depth partials live in the scan scratch: the item sort's first launch
-    // reduces them into the header (and resets it for the frame) before
-    // anything else uses that scratch
-    uint32_t *part = ws.scan_tmp;
+    // the item sort's first launch reduces the depth partials (and resets the
+    // header for the frame)
+    uint32_t *part = ws.depth_part;
     if (nb > 0 && ws.n_items >= kStreamItems && !colours)
         hipLaunchKernelGGL(k_preprocess<true>, dim3((unsigned)nb), dim3(kPreThreads), 0, s, ws, g, cams, p, part);
     else if (nb > 0)

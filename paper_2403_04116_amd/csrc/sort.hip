@@ -953,7 +953,7 @@ hipError_t radix_passes(const Ws &ws, int passes, int blocks, hipStream_t s,
 }  // namespace
 
 hipError_t launch_sort_items(const Ws &ws, const xg_camera *cams, const Params &p, hipStream_t s) {
-    // the preprocess left one depth (min, max) pair per workgroup in scan_tmp
+    // the preprocess left one depth (min, max) pair per workgroup
     const int64_t nparts = (ws.n_items + kPreThreads - 1) / kPreThreads;
     if (ws.view_sort != ViewSort::kNone) {
         if (ws.n > kViewSortMax) return hipErrorInvalidValue;
@@ -962,13 +962,13 @@ hipError_t launch_sort_items(const Ws &ws, const xg_camera *cams, const Params &
             if (ws.n > kViewListsItems * kViewSortThreads || ws.bin_ppv > kViewSortParts ||
                 ws.bin_ppv * ((ws.bin_tiles + 1) / 2) > view_sort_words(kViewListsItems))
                 return hipErrorInvalidValue;
-            hipLaunchKernelGGL((k_sort_view<kViewListsItems, true>), grid, block, 0, s, ws, cams, p.tile, ws.scan_tmp,
+            hipLaunchKernelGGL((k_sort_view<kViewListsItems, true>), grid, block, 0, s, ws, cams, p.tile, ws.depth_part,
                                nparts);
         } else if (ws.n <= kViewListsItems * kViewSortThreads) {
-            hipLaunchKernelGGL((k_sort_view<kViewListsItems, false>), grid, block, 0, s, ws, cams, p.tile, ws.scan_tmp,
+            hipLaunchKernelGGL((k_sort_view<kViewListsItems, false>), grid, block, 0, s, ws, cams, p.tile, ws.depth_part,
                                nparts);
         } else {
-            hipLaunchKernelGGL((k_sort_view<kViewSortItems, false>), grid, block, 0, s, ws, cams, p.tile, ws.scan_tmp,
+            hipLaunchKernelGGL((k_sort_view<kViewSortItems, false>), grid, block, 0, s, ws, cams, p.tile, ws.depth_part,
                                nparts);
         }
         return hipGetLastError();
@@ -978,9 +978,9 @@ hipError_t launch_sort_items(const Ws &ws, const xg_camera *cams, const Params &
     const int passes = (32 + kRadixBits - 1) / kRadixBits;
     if (passes > kMaxPasses) return hipErrorInvalidValue;
     switch (ws.item_per) {
-        case 2: return radix_passes<ItemSort<2>>(ws, passes, ws.item_blocks, s, ws.scan_tmp, nparts);
-        case 4: return radix_passes<ItemSort<4>>(ws, passes, ws.item_blocks, s, ws.scan_tmp, nparts);
-        case kItemSortItems: return radix_passes<ItemSort<kItemSortItems>>(ws, passes, ws.item_blocks, s, ws.scan_tmp, nparts);
+        case 2: return radix_passes<ItemSort<2>>(ws, passes, ws.item_blocks, s, ws.depth_part, nparts);
+        case 4: return radix_passes<ItemSort<4>>(ws, passes, ws.item_blocks, s, ws.depth_part, nparts);
+        case kItemSortItems: return radix_passes<ItemSort<kItemSortItems>>(ws, passes, ws.item_blocks, s, ws.depth_part, nparts);
         default: return hipErrorInvalidValue;
     }
 }
