@@ -429,19 +429,67 @@ __device__ __forceinline__ int order_bucket(const Ws &ws, int64_t t) {
 // is one contiguous block per XCD.  A bijection for any chunk > 0.
 struct TileDeal {
     int chunk, rounds, base, q, rem;
-    __device__ __forceinline__ TileDeal(int n, int c, bool contiguous)
+    __host__ __device__ __forceinline__ TileDeal(int n, int c, bool contiguous)
         : chunk(c), rounds(contiguous ? 0 : n / (kXcds * c)) {
         base = rounds * kXcds * chunk;
         q = (n - base) / kXcds;
         rem = (n - base) % kXcds;
     }
+    // tiles of XCD x
+    __host__ __device__ __forceinline__ int tiles(int x) const { return rounds * chunk + q + (x < rem ? 1 : 0); }
     // tile j (from 0) of XCD x
-    __device__ __forceinline__ int tile(int x, int j) const {
+    __host__ __device__ __forceinline__ int tile(int x, int j) const {
         const int dealt = rounds * chunk;
         if (j < dealt) return (j / chunk * kXcds + x) * chunk + j % chunk;
-        return base + x * q + min(x, rem) + (j - dealt);
+        return base + x * q + (x < rem ? x : rem) + (j - dealt);
     }
 };
+
+// The chunkings that xcd_order_block chooses from: step 0 is one contiguous
+// block per XCD, step m chunks of about n / (8 * 2^m) tiles, whole groups of g.
+constexpr int kDealSteps = 7;
+constexpr int kDealParts = 8;                        // threads per (step, XCD) sum
+constexpr float kDealSlack = 1.1f;
+__host__ __device__ __forceinline__ int deal_chunk(int n, int g, int step) {
+    const int c = n / (kXcds << step) / g * g;
+    return c > g ? c : g;
+}
+
+// List entries of XCD x under deal d, times g: the share of thread `part` of
+// kDealParts.  Whole groups of the dealt chunks (`group`: entries of every g
+// consecutive tiles); the left-over pieces start and end inside groups, whose
+// entries are taken as even over their tiles.  Every workgroup makes the
+// choice for itself and all have to make the same one, or tiles are rendered
+// twice and others never: integers, whose sum no order of adding changes
+// (below 2^31 entries x 2^20 tiles a group).
+__host__ __device__ __forceinline__ uint64_t deal_share(const uint32_t *group, int g, const TileDeal &d, int x,
+                                                        int part) {
+    const int tiles = d.tiles(x);
+    uint64_t sum = 0;
+    for (int j = part * g; j < tiles; j += kDealParts * g)
+        sum += (uint64_t)group[d.tile(x, j) / g] * (uint32_t)(tiles - j < g ? tiles - j : g);
+    return sum;
+}
+
+// The coarsest step within kDealSlack of an even split, else the most even one.
+__host__ __device__ __forceinline__ int deal_choice(const uint64_t (&load)[kDealSteps][kXcds]) {
+    int best = 0;
+    float best_max = 0.0f;
+#pragma unroll 1
+    for (int step = 0; step < kDealSteps; ++step) {
+        uint64_t mx = 0, total = 0;
+        for (int k = 0; k < kXcds; ++k) {
+            mx = load[step][k] > mx ? load[step][k] : mx;
+            total += load[step][k];
+        }
+        const float m = (float)mx * (kXcds / (float)(total > 0 ? total : 1));   // 1: even
+        if (step == 0 || (best_max > kDealSlack && m < best_max)) {
+            best = step;
+            best_max = m;
+        }
+    }
+    return best;
+}
 
 // Writes the cnt tiles tile_of(j) longest list first to out (buckets of an
 // eighth of an octave; the order inside a bucket is arbitrary).  The
@@ -484,15 +532,13 @@ __device__ __forceinline__ void order_tiles(const Ws &ws, int cnt, TileOf tile_o
 // view of 2048 x 1536 0.585 -> 0.518 ms, of 512^2 0.400 -> 0.389 ms; 200k,
 // 8 views of 512^2 (one view per XCD, kept contiguous) unchanged.
 constexpr int kOrderGroups = 2048;
-constexpr int kDealSteps = 7;
-constexpr int kDealParts = 8;                        // threads per (step, XCD) sum
-constexpr float kDealSlack = 1.1f;
 __device__ __forceinline__ void xcd_order_block(const Ws &ws, int x, uint32_t *hist, uint32_t *scan_lds,
                                                 uint32_t *group) {
-    static_assert(kDealSteps * kXcds * kDealParts <= 512, "one thread per partial sum");
+    static_assert(kDealSteps * kXcds * kDealParts <= 512 && kDealSteps * kXcds * kDealParts % kWave == 0,
+                  "one thread per partial sum, whole wavefronts");
     const int n = (int)ws.total_tiles;
     const TileDeal own(n, n, true);
-    const int cnt = own.q + (x < own.rem ? 1 : 0);
+    const int cnt = own.tiles(x);
     const int t0 = x * own.q + min(x, own.rem);
     // list entries of every group of g consecutive tiles (16 lanes a group)
     int g = 16;
@@ -509,45 +555,24 @@ __device__ __forceinline__ void xcd_order_block(const Ws &ws, int x, uint32_t *h
         for (int o = 8; o > 0; o >>= 1) len += (uint32_t)__shfl_xor((int)len, o, kWave);
         if (k < ng && threadIdx.x % 16 == 0) group[k] = len;
     }
-    __shared__ float s_load[kDealSteps][kXcds];
-    if (threadIdx.x < kDealSteps * kXcds) (&s_load[0][0])[threadIdx.x] = 0.0f;
+    __shared__ uint64_t s_load[kDealSteps][kXcds];
     __syncthreads();
-    auto chunk_of = [&](int step) { return max(n / (kXcds << step) / g * g, g); };
-    if (threadIdx.x < kDealSteps * kXcds * kDealParts) {
+    if (threadIdx.x < kDealSteps * kXcds * kDealParts) {   // (whole wavefronts)
         const int part = threadIdx.x % kDealParts, xx = threadIdx.x / kDealParts % kXcds;
         const int step = threadIdx.x / (kDealParts * kXcds);
-        const TileDeal d(n, chunk_of(step), step == 0);
-        const int tiles = d.rounds * d.chunk + d.q + (xx < d.rem ? 1 : 0);
-        // whole groups of the dealt chunks; the left-over pieces start and end
-        // inside groups, whose entries are taken as even over their tiles
-        float sum = 0.0f;
-        for (int j = part * g; j < tiles; j += kDealParts * g) {
-            const int t = d.tile(xx, j);
-            sum += (float)group[t / g] * ((float)min(g, tiles - j) / (float)g);
-        }
-        atomicAdd(&s_load[step][xx], sum);
+        const TileDeal d(n, deal_chunk(n, g, step), step == 0);
+        uint64_t sum = deal_share(group, g, d, xx, part);
+#pragma unroll
+        for (int o = kDealParts / 2; o > 0; o >>= 1) sum += (uint64_t)__shfl_xor((unsigned long long)sum, o, kWave);
+        if (part == 0) s_load[step][xx] = sum;
     }
     __syncthreads();
-    int best = 0;
-    float best_max = 0.0f;
-#pragma unroll
-    for (int step = 0; step < kDealSteps; ++step) {
-        float mx = 0.0f, total = 0.0f;
-        for (int k = 0; k < kXcds; ++k) {
-            mx = fmaxf(mx, s_load[step][k]);
-            total += s_load[step][k];
-        }
-        const float m = mx * (kXcds / fmaxf(total, 1.0f));   // 1: even
-        if (step == 0 || (best_max > kDealSlack && m < best_max)) {
-            best = step;
-            best_max = m;
-        }
-    }
+    const int best = deal_choice(s_load);
     order_tiles(ws, cnt, [&](int j) { return own.tile(x, j); }, ws.xcd_order + t0, hist, scan_lds);
     if (best == 0) {
         for (int j = (int)threadIdx.x; j < cnt; j += blockDim.x) ws.blend_order[t0 + j] = ws.xcd_order[t0 + j];
     } else {
-        const TileDeal d(n, chunk_of(best), false);
+        const TileDeal d(n, deal_chunk(n, g, best), false);
         order_tiles(ws, cnt, [&](int j) { return d.tile(x, j); }, ws.blend_order + t0, hist, scan_lds);
     }
 }
