@@ -455,37 +455,38 @@ __host__ __device__ __forceinline__ int deal_chunk(int n, int g, int step) {
     return c > g ? c : g;
 }
 
-// List entries of XCD x under deal d, times g: the share of thread `part` of
+// List entries of XCD x under deal d: the share of thread `part` of
 // kDealParts.  Whole groups of the dealt chunks (`group`: entries of every g
 // consecutive tiles); the left-over pieces start and end inside groups, whose
-// entries are taken as even over their tiles.  Every workgroup makes the
-// choice for itself and all have to make the same one, or tiles are rendered
-// twice and others never: integers, whose sum no order of adding changes
-// (below 2^31 entries x 2^20 tiles a group).
-__host__ __device__ __forceinline__ uint64_t deal_share(const uint32_t *group, int g, const TileDeal &d, int x,
+// entries are taken as even over their tiles, in sixteenths.  Every workgroup
+// makes the choice for itself and all have to make the same one, or tiles are
+// rendered twice and others never: integers, whose sum no order of adding
+// changes (a frame has fewer than 2^31 entries).
+__host__ __device__ __forceinline__ uint32_t deal_share(const uint32_t *group, int g, const TileDeal &d, int x,
                                                         int part) {
     const int tiles = d.tiles(x);
-    uint64_t sum = 0;
-    for (int j = part * g; j < tiles; j += kDealParts * g)
-        sum += (uint64_t)group[d.tile(x, j) / g] * (uint32_t)(tiles - j < g ? tiles - j : g);
+    uint32_t sum = 0;
+    for (int j = part * g; j < tiles; j += kDealParts * g) {
+        const uint32_t len = group[d.tile(x, j) / g];
+        sum += tiles - j >= g ? len : (uint32_t)((uint64_t)len * (uint32_t)((tiles - j) / (g / 16)) >> 4);
+    }
     return sum;
 }
 
+// The largest XCD's load over the mean (1: even).
+__host__ __device__ __forceinline__ float deal_excess(uint32_t largest, uint32_t total) {
+    return (float)largest * (kXcds / (float)(total > 0 ? total : 1));
+}
+
 // The coarsest step within kDealSlack of an even split, else the most even one.
-__host__ __device__ __forceinline__ int deal_choice(const uint64_t (&load)[kDealSteps][kXcds]) {
+__host__ __device__ __forceinline__ int deal_choice(const float (&excess)[kDealSteps]) {
     int best = 0;
-    float best_max = 0.0f;
-#pragma unroll 1
-    for (int step = 0; step < kDealSteps; ++step) {
-        uint64_t mx = 0, total = 0;
-        for (int k = 0; k < kXcds; ++k) {
-            mx = load[step][k] > mx ? load[step][k] : mx;
-            total += load[step][k];
-        }
-        const float m = (float)mx * (kXcds / (float)(total > 0 ? total : 1));   // 1: even
-        if (step == 0 || (best_max > kDealSlack && m < best_max)) {
+    float least = excess[0];
+#pragma unroll
+    for (int step = 1; step < kDealSteps; ++step) {
+        if (least > kDealSlack && excess[step] < least) {
             best = step;
-            best_max = m;
+            least = excess[step];
         }
     }
     return best;
@@ -534,8 +535,7 @@ __device__ __forceinline__ void order_tiles(const Ws &ws, int cnt, TileOf tile_o
 constexpr int kOrderGroups = 2048;
 __device__ __forceinline__ void xcd_order_block(const Ws &ws, int x, uint32_t *hist, uint32_t *scan_lds,
                                                 uint32_t *group) {
-    static_assert(kDealSteps * kXcds * kDealParts <= 512 && kDealSteps * kXcds * kDealParts % kWave == 0,
-                  "one thread per partial sum, whole wavefronts");
+    static_assert(kXcds * kDealParts == kWave && kDealSteps * kWave <= 512, "a wavefront per step");
     const int n = (int)ws.total_tiles;
     const TileDeal own(n, n, true);
     const int cnt = own.tiles(x);
@@ -555,19 +555,25 @@ __device__ __forceinline__ void xcd_order_block(const Ws &ws, int x, uint32_t *h
         for (int o = 8; o > 0; o >>= 1) len += (uint32_t)__shfl_xor((int)len, o, kWave);
         if (k < ng && threadIdx.x % 16 == 0) group[k] = len;
     }
-    __shared__ uint64_t s_load[kDealSteps][kXcds];
+    __shared__ float s_excess[kDealSteps];
     __syncthreads();
-    if (threadIdx.x < kDealSteps * kXcds * kDealParts) {   // (whole wavefronts)
+    if (threadIdx.x < kDealSteps * kWave) {   // a wavefront per step
         const int part = threadIdx.x % kDealParts, xx = threadIdx.x / kDealParts % kXcds;
-        const int step = threadIdx.x / (kDealParts * kXcds);
+        const int step = threadIdx.x / kWave;
         const TileDeal d(n, deal_chunk(n, g, step), step == 0);
-        uint64_t sum = deal_share(group, g, d, xx, part);
+        uint32_t load = deal_share(group, g, d, xx, part);
 #pragma unroll
-        for (int o = kDealParts / 2; o > 0; o >>= 1) sum += (uint64_t)__shfl_xor((unsigned long long)sum, o, kWave);
-        if (part == 0) s_load[step][xx] = sum;
+        for (int o = 1; o < kDealParts; o <<= 1) load += (uint32_t)__shfl_xor((int)load, o, kWave);
+        uint32_t total = load;
+#pragma unroll
+        for (int o = kDealParts; o < kWave; o <<= 1) {
+            load = max(load, (uint32_t)__shfl_xor((int)load, o, kWave));
+            total += (uint32_t)__shfl_xor((int)total, o, kWave);
+        }
+        if (threadIdx.x % kWave == 0) s_excess[step] = deal_excess(load, total);
     }
     __syncthreads();
-    const int best = deal_choice(s_load);
+    const int best = deal_choice(s_excess);
     order_tiles(ws, cnt, [&](int j) { return own.tile(x, j); }, ws.xcd_order + t0, hist, scan_lds);
     if (best == 0) {
         for (int j = (int)threadIdx.x; j < cnt; j += blockDim.x) ws.blend_order[t0 + j] = ws.xcd_order[t0 + j];

@@ -20,15 +20,20 @@ using namespace xg;
 // the choice with every (step, XCD) load's shares added in the order order[]
 extern "C" int choose(const uint32_t *group, int n, int g, const int32_t *order) {
     std::remove_cv_t<std::remove_reference_t<decltype(deal_share(group, g, TileDeal(n, n, true), 0, 0))>> zero = 0;
-    decltype(zero) load[kDealSteps][kXcds];
-    for (int s = 0; s < kDealSteps; ++s)
+    float excess[kDealSteps];
+    for (int s = 0; s < kDealSteps; ++s) {
+        decltype(zero) largest = zero, total = zero;
         for (int x = 0; x < kXcds; ++x) {
             const TileDeal d(n, deal_chunk(n, g, s), s == 0);
-            load[s][x] = zero;
+            decltype(zero) load = zero;
             for (int p = 0; p < kDealParts; ++p)
-                load[s][x] += deal_share(group, g, d, x, order[(s * kXcds + x) * kDealParts + p]);
+                load += deal_share(group, g, d, x, order[(s * kXcds + x) * kDealParts + p]);
+            largest = load > largest ? load : largest;
+            total += load;
         }
-    return deal_choice(load);
+        excess[s] = deal_excess(largest, total);
+    }
+    return deal_choice(excess);
 }
 extern "C" int words() { return kDealSteps * kXcds * kDealParts; }
 // the tiles in launch order under step s
@@ -37,7 +42,7 @@ extern "C" void tiles(int n, int g, int s, int32_t *out) {
     for (int x = 0; x < kXcds; ++x)
         for (int j = 0; j < d.tiles(x); ++j) *out++ = d.tile(x, j);
 }
-// its exact loads in floating point, for the ties the cases are built from
+// the loads
 extern "C" void loads(const uint32_t *group, int n, int g, double *out) {
     for (int s = 0; s < kDealSteps; ++s)
         for (int x = 0; x < kXcds; ++x) {
