@@ -492,13 +492,14 @@ __host__ __device__ __forceinline__ int deal_choice(const float (&excess)[kDealS
     return best;
 }
 
-// Writes the cnt tiles tile_of(j) longest list first to out (buckets of an
-// eighth of an octave; the order inside a bucket is arbitrary).  The
+// Writes the cnt tiles tile_of(j) longest list first to out, and to also
+// unless null (buckets of an eighth of an octave; the order inside a bucket
+// is arbitrary).  The
 // workgroup has at least kOrderBuckets threads; hist: kOrderBuckets words
 // of LDS; scan_lds: kScanLds words.  Contains barriers.
 template <class TileOf>
-__device__ __forceinline__ void order_tiles(const Ws &ws, int cnt, TileOf tile_of, int32_t *out, uint32_t *hist,
-                                            uint32_t *scan_lds) {
+__device__ __forceinline__ void order_tiles(const Ws &ws, int cnt, TileOf tile_of, int32_t *out, int32_t *also,
+                                            uint32_t *hist, uint32_t *scan_lds) {
     for (int b = threadIdx.x; b < kOrderBuckets; b += blockDim.x) hist[b] = 0;
     __syncthreads();
     for (int j = (int)threadIdx.x; j < cnt; j += blockDim.x) atomicAdd(&hist[order_bucket(ws, tile_of(j))], 1u);
@@ -510,7 +511,9 @@ __device__ __forceinline__ void order_tiles(const Ws &ws, int cnt, TileOf tile_o
     __syncthreads();
     for (int j = (int)threadIdx.x; j < cnt; j += blockDim.x) {
         const int t = tile_of(j);
-        out[atomicAdd(&hist[order_bucket(ws, t)], 1u)] = (int32_t)t;
+        const uint32_t pos = atomicAdd(&hist[order_bucket(ws, t)], 1u);
+        out[pos] = (int32_t)t;
+        if (also) also[pos] = (int32_t)t;
     }
     __syncthreads();
 }
@@ -527,12 +530,25 @@ __device__ __forceinline__ void order_tiles(const Ws &ws, int cnt, TileOf tile_o
 // 4 ... 64, the coarsest within kDealSlack of an even split is taken, else
 // the most even one.  The entries are counted in groups of consecutive
 // tiles (`group` words of LDS, kOrderGroups of them), every workgroup over
-// the whole frame; the workgroup has 512 or 1024 threads.
+// the whole frame, by 16 tiles of a group (order_sample): all of them up to
+// 32 768 tiles, and never more than those reads.  The workgroup has 512 or
+// 1024 threads.  (64 Gaussians in 1000 views of 512 x 512, 1M tiles, the list
+// scatter with these workgroups in it: 509 us with every tile read, now 176;
+// 1000 Gaussians in 500 such views 266 -> 121.)
 // Measured (whole step, contiguous blocks -> dealt): 300k Gaussians, 32
 // views of 128^2, 256^2 and 512^2 in that order 2.87 -> 2.04 ms; 200k, one
 // view of 2048 x 1536 0.585 -> 0.518 ms, of 512^2 0.400 -> 0.389 ms; 200k,
 // 8 views of 512^2 (one view per XCD, kept contiguous) unchanged.
 constexpr int kOrderGroups = 2048;
+
+// The tile that lane l of 16 reads of group k of g tiles (g a power of two
+// from 16 on): one of its g / 16, at a place that differs from group to group
+// and lane to lane, or it would be the same column of the detector every time.
+__host__ __device__ __forceinline__ int64_t order_sample(int k, int l, int g) {
+    const uint32_t h = ((uint32_t)k * 16u + (uint32_t)l) * 0x9e3779b1u;   // (multiplicative hashing)
+    return (int64_t)k * g + (int64_t)l * (g / 16) + (int64_t)((h >> 8) & (uint32_t)(g / 16 - 1));
+}
+
 __device__ __forceinline__ void xcd_order_block(const Ws &ws, int x, uint32_t *hist, uint32_t *scan_lds,
                                                 uint32_t *group) {
     static_assert(kXcds * kDealParts == kWave && kDealSteps * kWave <= 512, "a wavefront per step");
@@ -540,20 +556,26 @@ __device__ __forceinline__ void xcd_order_block(const Ws &ws, int x, uint32_t *h
     const TileDeal own(n, n, true);
     const int cnt = own.tiles(x);
     const int t0 = x * own.q + min(x, own.rem);
-    // list entries of every group of g consecutive tiles (16 lanes a group)
+    // list entries of every group of g consecutive tiles (16 lanes a group),
+    // four groups' loads together
     int g = 16;
     while ((n + g - 1) / g > kOrderGroups) g *= 2;
-    const int ng = (n + g - 1) / g;
-    for (int k0 = 0; k0 < ng; k0 += blockDim.x / 16) {
-        const int k = k0 + (int)threadIdx.x / 16;
-        uint32_t len = 0;
-        for (int j = (int)threadIdx.x % 16; j < g; j += 16) {
-            const int64_t t = (int64_t)k * g + j;
-            if (k < ng && t < n) len += ws.ranges[2 * t + 1] - ws.ranges[2 * t];
+    const int ng = (n + g - 1) / g, lanes = (int)blockDim.x / 16;
+    const uint2 *rg = reinterpret_cast<const uint2 *>(ws.ranges);
+    for (int k0 = (int)threadIdx.x / 16; k0 - (int)threadIdx.x / 16 < ng; k0 += 4 * lanes) {
+        uint2 r[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t t = order_sample(k0 + u * lanes, (int)threadIdx.x % 16, g);
+            r[u] = t < n ? rg[t] : make_uint2(0u, 0u);
         }
 #pragma unroll
-        for (int o = 8; o > 0; o >>= 1) len += (uint32_t)__shfl_xor((int)len, o, kWave);
-        if (k < ng && threadIdx.x % 16 == 0) group[k] = len;
+        for (int u = 0; u < 4; ++u) {
+            uint32_t len = r[u].y - r[u].x;
+#pragma unroll
+            for (int o = 8; o > 0; o >>= 1) len += (uint32_t)__shfl_xor((int)len, o, kWave);
+            if (k0 + u * lanes < ng && threadIdx.x % 16 == 0) group[k0 + u * lanes] = len;
+        }
     }
     __shared__ float s_excess[kDealSteps];
     __syncthreads();
@@ -574,12 +596,11 @@ __device__ __forceinline__ void xcd_order_block(const Ws &ws, int x, uint32_t *h
     }
     __syncthreads();
     const int best = deal_choice(s_excess);
-    order_tiles(ws, cnt, [&](int j) { return own.tile(x, j); }, ws.xcd_order + t0, hist, scan_lds);
-    if (best == 0) {
-        for (int j = (int)threadIdx.x; j < cnt; j += blockDim.x) ws.blend_order[t0 + j] = ws.xcd_order[t0 + j];
-    } else {
+    order_tiles(ws, cnt, [&](int j) { return own.tile(x, j); }, ws.xcd_order + t0,
+                best == 0 ? ws.blend_order + t0 : nullptr, hist, scan_lds);
+    if (best != 0) {
         const TileDeal d(n, deal_chunk(n, g, best), false);
-        order_tiles(ws, cnt, [&](int j) { return d.tile(x, j); }, ws.blend_order + t0, hist, scan_lds);
+        order_tiles(ws, cnt, [&](int j) { return d.tile(x, j); }, ws.blend_order + t0, nullptr, hist, scan_lds);
     }
 }
 

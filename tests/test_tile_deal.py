@@ -42,6 +42,11 @@ extern "C" void tiles(int n, int g, int s, int32_t *out) {
     for (int x = 0; x < kXcds; ++x)
         for (int j = 0; j < d.tiles(x); ++j) *out++ = d.tile(x, j);
 }
+extern "C" void sample(int ng, int g, int64_t *out) {
+    for (int k = 0; k < ng; ++k)
+        for (int l = 0; l < 16; ++l) *out++ = order_sample(k, l, g);
+}
+extern "C" int groups() { return kOrderGroups; }
 // the loads
 extern "C" void loads(const uint32_t *group, int n, int g, double *out) {
     for (int s = 0; s < kDealSteps; ++s)
@@ -134,3 +139,43 @@ def test_choice_takes_an_even_split(lib):
     assert loads[0].max() > 7.0 * loads[0].mean()
     best = lib.choose(_ptr(heavy), n, g, _ptr(order))
     assert best > 0 and loads[best].max() <= 1.1 * loads[best].mean()
+
+
+@pytest.mark.parametrize("n", [1, 100, 32_768, 32_769, 262_147, 1_024_000, 1 << 27])
+def test_order_reads_a_bounded_number_of_tiles(lib, n):
+    g = _group_tiles(n)
+    ng = -(-n // g)
+    assert ng <= lib.groups() == 2048
+    out = np.zeros(16 * ng, np.int64)
+    lib.sample(ng, g, _ptr(out))
+    # one tile of every stretch of g / 16: at most 32 768, every tile of small frames
+    np.testing.assert_array_equal(out // (g // 16), np.arange(16 * ng))
+    if n <= 32_768:
+        np.testing.assert_array_equal(out, np.arange(16 * ng))
+    elif g >= 512:      # no column of 32 taken more than twice as often as its share
+        assert np.bincount(out % 32, minlength=32).max() < 2 * out.size / 32
+
+
+def _sampled_choice(lib, lens):
+    n = lens.size
+    g = _group_tiles(n)
+    ng = -(-n // g)
+    t = np.zeros(16 * ng, np.int64)
+    lib.sample(ng, g, _ptr(t))
+    group = np.where(t < n, lens[np.minimum(t, n - 1)], 0).reshape(ng, 16).sum(1).astype(np.uint32)
+    order = np.tile(np.arange(8), lib.words() // 8).astype(np.int32)
+    return lib.choose(_ptr(group), n, g, _ptr(order)), g
+
+
+def test_choice_from_the_sample(lib):
+    y, x = np.mgrid[-1:1:32j, -1:1:32j]
+    view = (40 * np.exp(-3 * (x * x + y * y))).astype(np.int64).ravel()      # 512 x 512, centre heavy
+    assert _sampled_choice(lib, np.tile(view, 1000))[0] == 0                   # equal views: contiguous
+    lens = np.concatenate([np.tile(view, 400), np.full(600 * 16, 300)])        # small views last, long lists
+    best, g = _sampled_choice(lib, lens)
+    assert best > 0
+    out = np.zeros(lens.size, np.int32)
+    lib.tiles(lens.size, g, best, _ptr(out))
+    split = [c.sum() for c in np.array_split(lens[out], 8)]
+    whole = [c.sum() for c in np.array_split(lens, 8)]
+    assert max(whole) > 1.3 * np.mean(whole) and max(split) < 1.15 * np.mean(split)
