@@ -783,7 +783,7 @@ __global__ __launch_bounds__(kViewSortThreads) void k_sort_view(Ws ws, const xg_
         __syncthreads();
         const bool ok = all <= (uint64_t)ws.cap;
         if (v == 0 && tid == 0) {
-            ws.hdr->n_pairs = (int32_t)all;
+            ws.hdr->n_pairs = (int32_t)min(all, 0x7fffffffu);   // (at most 2^16 items x 36 864 tiles: below 2^32)
             if (!ok) ws.hdr->status = XG_ECAPACITY;
         }
         // partition starts
