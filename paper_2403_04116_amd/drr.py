@@ -143,8 +143,6 @@ class Frame:
     def _status_pairs(self, then=None) -> tuple[int, int]:
         """status() and n_pairs() in one read; ``then`` is called (to enqueue
         more work) between its start and the wait for it."""
-        if torch.cuda.is_current_stream_capturing():
-            raise RuntimeError("the status word cannot be waited for while the stream is being captured")
         first = min(self.layout.status, self.layout.n_pairs)
         i, j = (self.layout.status - first) // 4, (self.layout.n_pairs - first) // 4
         words = torch.empty(max(i, j) + 1, dtype=torch.int32, pin_memory=True)
@@ -196,7 +194,10 @@ class Frame:
         """fit_capacity(), with a render of the lists into ``out`` (unless
         None) enqueued before the host waits for the status, so that the device
         has work when the host goes on (the blend of a failed list build reads
-        empty lists)."""
+        empty lists).  Refused, before anything is enqueued or marked, while the
+        stream is being captured: the status could not be waited for."""
+        if torch.cuda.is_current_stream_capturing():
+            raise RuntimeError("the status word cannot be waited for while the stream is being captured")
         for last in (False, True):
             self.preprocess_sort(g)
             status, p = self._status_pairs(None if out is None else lambda: self.render_fwd(g, out))
