@@ -557,9 +557,10 @@ __device__ __forceinline__ void finish_queue(int32_t *queue, int32_t *done) {
 // tiles from the work queue; otherwise one workgroup per tile.
 // STORE = true: also keep the transmittance before each of the first
 // ts.slots contributors of every pixel (one workgroup per tile only).
-// (64 registers: as for the backward below)
+// (64 registers for all variants of several wavefronts but the persistent
+// ones: as for the backward below)
 template <int T, int B, bool COUNT, bool PERSIST, bool STORE>
-__global__ __launch_bounds__(T * T, T > 8 && !PERSIST && !STORE && !COUNT ? 8 : 2) void k_render_fwd(Ws ws, const xg_camera *cams, Params p,
+__global__ __launch_bounds__(T * T, T > 8 && !PERSIST ? 8 : 2) void k_render_fwd(Ws ws, const xg_camera *cams, Params p,
                                                       float *image, float *final_t,
                                                       int32_t *n_contrib, int32_t *counts,
                                                       TStore ts, L1Fuse l1) {
@@ -846,9 +847,13 @@ __device__ __forceinline__ void bwd_tile(int tile, const Ws &ws, const xg_camera
 }
 
 // (64 registers for the plain variants of several wavefronts: 8 wavefronts
-// per SIMD, and two workgroups per CU of 32 x 32 tiles)
+// per SIMD, and two workgroups per CU of 32 x 32 tiles.  The stored variant
+// of 32 x 32 tiles too, for the same reason: with 72 registers one workgroup
+// to a CU, 200k Gaussians x 8 views of 512 x 512 forward 421 us and backward
+// 887 where two take 301 and 632, four spilled registers included.  At 16 x 16
+// a workgroup is 4 wavefronts and 70 registers cost nothing: 442 and 441.)
 template <int T, int B, bool PERSIST, bool STORE>
-__global__ __launch_bounds__(T * T, T > 8 && !PERSIST && !STORE ? 8 : 2) void k_render_bwd(Ws ws, const xg_camera *cams, Params p,
+__global__ __launch_bounds__(T * T, T > 8 && !PERSIST && (T > 16 || !STORE) ? 8 : 2) void k_render_bwd(Ws ws, const xg_camera *cams, Params p,
                                                       const float *dl_dimage, const float *final_t,
                                                       const int32_t *n_contrib, TStore ts) {
     __shared__ BlendLds<T, B, true> sh;
