@@ -47,13 +47,14 @@ if ROOT not in sys.path:
 # transcendental counts 4: quarter rate), per unit of work of the definition:
 #   forward: 21 per evaluation (offset, exponent, exp, opacity, clamp, test,
 #            transmittance update, accumulate);
-#   backward: 35 per revisited evaluation (recompute alpha, recover T by
-#            division, the 7 gradient terms) plus, per (Gaussian, wavefront)
-#            with a contributing lane, 42 wavefront instructions (the 7-value
-#            wavefront reduction and its atomics) = 42 x 64 lane slots.
+#   backward: 32 per revisited evaluation (recompute alpha, recover T by
+#            division, the 4 gradient terms that are summed over pixel rows)
+#            plus, per (Gaussian, wavefront) with a contributing lane, 13
+#            wavefront instructions (row sums, moment products, column sums:
+#            52 for four such pairs) = 13 x 64 lane slots.
 LANE_OPS_EVAL_FWD = 21
-LANE_OPS_EVAL_BWD = 35
-WAVE_INSTR_REDUCTION = 42
+LANE_OPS_EVAL_BWD = 32
+WAVE_INSTR_REDUCTION = 13
 WAVE = 64
 # MI355X: 256 CUs x 64 FP32 lanes x 2.4 GHz = 39.3 T lane-operations/s without
 # packed FP32 (what these scalar-FP32 kernels can issue); the published FP32
@@ -761,10 +762,10 @@ def main():
                      "work_model": f"fwd {LANE_OPS_EVAL_FWD}/evaluation; bwd {LANE_OPS_EVAL_BWD}/"
                                    f"revisited evaluation + {WAVE_INSTR_REDUCTION} x {WAVE} per "
                                    "(Gaussian, wavefront) reduction",
-                     "note": "the model prices each reduction as a 6-level butterfly per value "
-                             f"({WAVE_INSTR_REDUCTION} wavefront instructions); the backward's "
-                             "reduce-scatter issues about 13 per entry, so the model's lane "
-                             "operations exceed the instructions issued and frac can pass 1"},
+                     "note": "evaluations are the definition's (every pixel of a listed "
+                             "Gaussian's rectangle up to termination), of which the kernels skip "
+                             "a share and to which they add list and mask work; the VALU-busy "
+                             "share of the launch is a counter's, in profiles/"},
         "cpu_baseline": cpu,
         "graph": graph,
         "eager": eager,

@@ -191,10 +191,12 @@ xg_status xg_preprocess(const xg_frame *f /* [host] */, const xg_gaussians *g /*
  * depth.  The (view, Gaussian) items of each view are radix-sorted stably
  * by depth on the depth bits that vary, and their tile counts are scanned
  * in that order (offsets).  One (global tile id, Gaussian index) pair per
- * (view, Gaussian, tile) is then placed in tile order: unless the views
- * have very many tiles, directly at its list position by a stable counting
- * sort of each view's pairs by tile; otherwise emitted in item order and
- * radix-sorted stably by tile id.  A tile lists only Gaussians of its own
+ * (view, Gaussian, tile) is then placed in tile order: directly at its list
+ * position by a stable counting sort of each view's pairs by tile, when no
+ * view has more than 1024 tiles in a row and either none has more than 4096
+ * tiles, or none more than 65 536 and the frame few enough items (at most
+ * 4096 partitions of its views' items times bands of 1024 tiles); otherwise
+ * emitted in item order and radix-sorted stably by tile id.  A tile lists only Gaussians of its own
  * view, so either way the result equals a sort of the keys (tile << 32 |
  * float32 bits of the depth), ties by ascending Gaussian index.  Also
  * fills the per-tile [start, end) ranges and the pair count; more pairs
@@ -206,7 +208,8 @@ xg_status xg_preprocess(const xg_frame *f /* [host] */, const xg_gaussians *g /*
  * near the end of a launch; where those blocks hold very different numbers
  * of list entries, the tiles are dealt to the XCDs in smaller chunks
  * instead (an internal copy of the order; any order gives the same
- * results). */
+ * results).  May be repeated on one preprocess: every call builds the same
+ * lists. */
 xg_status xg_bin_sort(const xg_frame *f /* [host] */, void *stream);
 
 /* Stage 3 (Eq. 10): front-to-back blending of every pixel over its tile's

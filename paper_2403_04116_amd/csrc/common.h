@@ -227,16 +227,20 @@ __device__ __forceinline__ uint64_t match_peers(uint32_t d, bool valid) {
 }
 
 // Tile lists by counting: most items per partition (all of one view), pairs
-// per LDS window of the ranking kernel, and the most tiles a view may have on
-// this path (larger views use emission and the radix sort of the pairs).
+// per LDS window of the ranking kernel, and which frames take this path (the
+// others use emission and the radix sort of the pairs; the rule and its
+// figures are where the frame's plan is made): no view with more than
+// kBinMaxTilesX tiles in a row, and either none with more than kBinMaxTiles
+// tiles, or none with more than kBinMostTiles and at most kBinMostGroups
+// ranking workgroups.
 constexpr int kBinItems = 2048;
 constexpr int kBinItemsMin = 256;
 constexpr int kBinResident = 512;   // ranking workgroups the device holds at once (two per CU)
 constexpr int kBinWindow = 4096;
 constexpr int kBinMaxTiles = 4096;
-constexpr int kBinMaxTilesX = 1024;             // most tiles in a row
-constexpr int kBinMostTiles = 65536;            // most tiles of a view in a frame of few
-constexpr int kBinMostGroups = 4096;            // ranking workgroups
+constexpr int kBinMaxTilesX = 1024;             // a band of the ranking kernel holds a row
+constexpr int kBinMostTiles = 65536;
+constexpr int kBinMostGroups = 4096;
 constexpr int kColTiles = 64;                   // tiles of a workgroup of the column scans
 
 constexpr int kScanThreads = 256;
@@ -274,7 +278,11 @@ constexpr int kSortCtlWords = (kMaxPasses * kRadix + kMaxPasses) * kGhStride;
 // 62 500 (16 M items) the launch is the cheaper one.
 constexpr int64_t kFoldParts = 8192;
 
-// The item sort's words that are zero before its histogram launch.
+// The item sort's words that are zero before its histogram launch where that
+// launch folds the depth partials (ws.sort_fold): the digit totals of every
+// view and the partition counters.  The preprocess zeroes them, and the launch
+// after the sort again, so that a second list build of the same preprocess
+// finds them zero too.
 __device__ __forceinline__ int64_t item_sort_zeros(const Ws &ws) {
     return (int64_t)ws.n_views * kMaxPasses * (kRadix + 1);
 }

@@ -206,12 +206,6 @@ __device__ __forceinline__ uint32_t *part_counter(const Ws &ws, int64_t segment,
     return S::kSegmented ? ws.vctr + (segment * kMaxPasses + pass) * kGhStride : ws.pctr + pass * kGhStride;
 }
 
-// Words of the item sort that are zero between frames where its histogram
-// launch folds the depth partials (ws.sort_fold): the digit totals of every
-// view and the partition counters.  The preprocess zeroes them, and the
-// launch after the sort again, so that a second list build of the same
-// preprocess finds them zero too.
-
 // Zeroes the digit histograms, partition counters and the first pass's
 // look-back words of one sort.  The item sort's (depth_part set) also
 // resets the frame header (workgroup 0) and folds the preprocess's depth

@@ -1,6 +1,8 @@
 """xg_bin_sort repeated on one preprocess where a view has more tiles than the
 counting path takes (pairs emitted and radix sorted by tile), for every form of
-the item sort: each build gives the oracle's lists.  The Gaussians are ordered
+the item sort: each build gives the oracle's lists.  (A 1100 x 1100 view at 8 x 8
+tiles with a few thousand Gaussians is counted in bands; the sizes here and the
+last ones of test_gpu_bands.py take the pair sort.)  The Gaussians are ordered
 farthest first, so that the depth range of the first 256 items decides."""
 import math
 
