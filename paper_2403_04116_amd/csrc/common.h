@@ -541,8 +541,8 @@ __device__ __forceinline__ void order_tiles(const Ws &ws, int cnt, TileOf tile_o
 // the whole frame, by 16 tiles of a group (order_sample): all of them up to
 // 32 768 tiles, and never more than those reads.  The workgroup has 512 or
 // 1024 threads.  (64 Gaussians in 1000 views of 512 x 512, 1M tiles, the list
-// scatter with these workgroups in it: 509 us with every tile read, now 176;
-// 1000 Gaussians in 500 such views 266 -> 121.)
+// scatter with these workgroups in it: 509 us with every tile read, now 171;
+// 1000 Gaussians in 500 such views 266 -> 117.)
 // Measured (whole step, contiguous blocks -> dealt): 300k Gaussians, 32
 // views of 128^2, 256^2 and 512^2 in that order 2.87 -> 2.04 ms; 200k, one
 // view of 2048 x 1536 0.585 -> 0.518 ms, of 512^2 0.400 -> 0.389 ms; 200k,
